@@ -30,17 +30,17 @@ sys.path.insert(0, ROOT)
 METRIC = "scatterer-sample terms/s (P*M*N*Ns*L/s) MFMA vs FP64-direct at stated err; p50/p99"
 PEAK_FP16 = 2.5e15     # dense fp16 matrix flop/s, MI355X
 PEAK_FP64 = 78.6e12    # fp64 vector flop/s, MI355X
-FLOP_MFMA = 24         # 3 split products x complex MAC (4 real MACs) x 2
+FLOP_MFMA = 12         # 3 split products x 2 real MACs (a mirrored sample pair shares 4) x 2
 FLOP_PLAIN = 8         # one binary64 complex MAC
 
-# HBM bytes per launch of k_mfma_split16 on the headline frame: rocprofv3 --pmc
+# HBM bytes per launch of k_mfma_mirror on the headline frame: rocprofv3 --pmc
 # FETCH_SIZE and WRITE_SIZE (KiB per dispatch) scaled by what the same counters
 # read for a 1 GiB device copy (fetch x 2.0, write x 1.0).  They hold only for
 # the kernel sources they were taken on; any change to those sources turns
 # the figure into null until the counters are taken again.
-TRAFFIC = {"sources": ("rs_mfma.hip", "rs_device.h", "rs_internal.h", "rs_split16.h"),
-           "sources_sha256": "44849d3c15d1a5854c90d8e613516197a2a84f380176b3013655c7f83f33458a",
-           "fetch_bytes": 2.0 * 5289 * 1024, "write_bytes": 65362 * 1024}
+TRAFFIC = {"sources": ("rs_mirror.hip", "rs_device.h", "rs_internal.h", "rs_split16.h"),
+           "sources_sha256": "ee697c0f19235eea98052e24ba53d14bd2656c22d9740b96fde914d0ade32ab0",
+           "fetch_bytes": 2.0 * 7251 * 1024, "write_bytes": 71064 * 1024}
 # The same for one rs_range_doppler_ws call on the 100-frame walk (k_rd_fused,
 # k_rd_merge, k_rd_peak summed).
 RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_fft.h"),
@@ -270,7 +270,7 @@ def main():
         "kernel_timing": "HIP events around the contraction kernel of every 4th timed step",
         "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK_FP16 / 1e12,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP16, "traffic": measured_traffic(),
-                     "kernel": "k_mfma_split16", "kernel_ms": kavg,
+                     "kernel": "k_mfma_mirror", "kernel_ms": kavg,
                      "flop_per_term": FLOP_MFMA, "terms_per_launch": terms,
                      "traffic_unit": "HBM bytes per launch",
                      "algorithmic_bytes": 20 * px.P + 8 * radar.C * radar.L * radar.Ns},

@@ -32,7 +32,10 @@
  *                         per-channel complex contraction
  *                         Y_c = F_c^T diag(sigma_c) D done on fp16 matrix
  *                         cores with fp32 accumulation (hi*hi + hi*lo +
- *                         lo*hi).  Typical relative L2 error vs an exact
+ *                         lo*hi): complex128 plans sample by sample,
+ *                         complex64 plans with fast time taken from its
+ *                         middle, mirrored samples sharing their cosine and
+ *                         sine sums (half the products).  Typical relative L2 error vs an exact
  *                         binary64 sum: 1e-6 .. 1e-5.
  *   RS_FORM_NUFFT         per channel a two-dimensional type-1 non-uniform
  *                         FFT from the points (b, -beta) onto the Ns x L
@@ -185,17 +188,17 @@ rs_status rs_cube_plan_nufft(const rs_radar *radar, rs_dtype dtype, int64_t max_
  * (0 <= P <= max_pixels).  Errors: RS_E_INVALID. */
 rs_status rs_plan_workspace_bytes(const rs_plan *plan, int64_t P, size_t *bytes);
 
-/* Matrix-core tile configurations are named "WNxTLxNW" -- rows per wave x
- * columns (l) x waves per workgroup; the library builds 64x128x4, 32x128x4,
- * 32x128x8, 32x64x4, 32x64x8, 64x64x4, 64x64x8 and 128x64x4 -- with an
- * optional suffix 'i' on the 8-wave shapes.  8-wave shapes run two waves
- * per SIMD with their matrix and vector work phase-shifted against each
- * other; with 'i' they run the software-pipelined interleave (each wave
- * alternates matrix groups with staged slices of phasor work), which the
- * 4-wave shapes always run (the suffix is accepted there and changes
- * nothing).  The two schedules of a shape give the same cube bit for bit;
- * different shapes chunk the pixels differently and so differ in the last
- * bits, all within the form's error. */
+/* Matrix-core tile configurations are named "WNxTLxNW": a work item covers
+ * WN * NW fast-time samples (n) x TL blocks (l) with a workgroup of NW waves;
+ * the library builds 64x128x4, 32x128x4, 32x128x8, 32x64x4, 32x64x8, 64x64x4,
+ * 64x64x8 and 128x64x4 -- with an optional suffix 'i' on the 8-wave shapes.
+ * 8-wave shapes run two waves per SIMD with their matrix and vector work
+ * phase-shifted against each other; with 'i' both waves of a SIMD run the
+ * same order (each alternates matrix instructions with slices of phasor
+ * work), which the 4-wave shapes always run (the suffix is accepted there and
+ * changes nothing).  The two schedules of a shape give the same cube bit for
+ * bit; different shapes chunk the pixels differently and so differ in the
+ * last bits, all within the form's error. */
 
 /* Sets the matrix-core tile configuration of `plan` (see above).  It changes
  * the plan: call it before the plan is shared, never while other calls use
@@ -208,7 +211,7 @@ rs_status rs_plan_set_tile(rs_plan *plan, const char *tile);
  * again with 'i') synthesises `pixels` into `cube` once to warm up and
  * `reps` times timed with HIP events on `hip_stream`, and the one with the
  * smallest mean time is kept (the plan's own choice otherwise comes from a
- * rule measured on the frame and batch workloads).  The call synchronises
+ * rule measured on full launches).  The call synchronises
  * the stream and leaves the last synthesis in `cube`.  It changes the plan:
  * call it before the plan is shared, never while other calls use it.  Plans
  * of the other forms are left unchanged.  chosen (may be NULL) receives the

@@ -49,7 +49,9 @@ rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *ch
     int64_t s_target = pl->items_target / tiles;
     if (s_target < 1) s_target = 1;
     int64_t ch = (P + s_target - 1) / s_target;
-    ch = round_up(ch, 16);
+    // mirrored pairs: whole pairs of 32-pixel steps (that kernel runs its
+    // steps in pairs)
+    ch = round_up(ch, pl->mirror ? 64 : 16);
     if (ch < pl->min_chunk) ch = pl->min_chunk;
     if (ch > (int64_t)1 << 30) return rs_fail(RS_E_INVALID, "pixel count too large");
     *chunk = (int32_t)ch;
@@ -221,6 +223,8 @@ rs_status rs_launch_main(const rs_plan *pl, const rs_launch &L, bool block_stren
     const bool timed = rs_timer_begin(st);
     if (pl->form == RS_FORM_FP64_DIRECT)
         rs_launch_plain(L, pl->tl, grid, st);
+    else if (pl->mirror)
+        rs_launch_mirror(L, pl->wn, pl->tl, pl->nw, pl->interleave != 0, block_strength, grid, st);
     else
         rs_launch_mfma(L, pl->wn, pl->tl, pl->nw, pl->interleave != 0, block_strength, grid, st);
     hipError_t e = hipGetLastError();
@@ -336,6 +340,7 @@ static rs_status plan_common(const rs_radar *r, rs_form form, rs_dtype dtype, in
     pl->form = form;
     pl->dtype = dtype;
     pl->max_pixels = max_pixels;
+    pl->mirror = form == RS_FORM_MFMA_SPLIT16 && dtype == RS_C64;
     rs_choose_tiles(pl);
     std::vector<float> deconv;
     if (form == RS_FORM_NUFFT) {
@@ -387,25 +392,42 @@ void rs_choose_tiles(rs_plan *pl)
         pl->min_chunk = 256;
         pl->occupancy = 2;
     } else {
-        // Matrix-core tiles: TL columns (l), NW waves of WN rows (n).
-        //   L > 64: 128 columns; 8 waves x 32 rows (two waves per SIMD) when
-        //           Ns > 128, else 4 waves x 32 rows
-        //   L <= 64: 64 columns; 4 waves x 64 rows (Ns > 128) or x 32 rows
-        int wn, tl, nw;
-        if (pl->L > 64) {
-            tl = 128;
-            wn = 32;
-            nw = pl->Ns > 128 ? 8 : 4;
+        if (pl->mirror) {
+            // Mirrored pairs: tiles of NW*WN samples (n) x TL blocks (l): the shape
+            // whose tiles cover Ns x L in the least time.  cost: ns per pixel and
+            // work item of a full launch (measured with 12 and 192 channels at
+            // Ns 64..512, L 32..256): larger tiles evaluate fewer phasors per
+            // term, but an Ns or L that leaves most of a tile empty pays for all
+            // of it.  E.g. Ns 384, L 100: 32x128x4 0.216 ms (three tiles), 32x128x8
+            // 0.242 ms (two, half of the second empty).  At equal cost the larger
+            // tile (fewer partial sums).  8-wave shapes of 64 blocks take the
+            // pipelined schedule (1-3 % faster than phase-shifted waves there).
+            // No tile exceeds 256 x 128 cells, so that ncu work items keep the
+            // partial sums within the static scratch.
+            static const struct { int wn, tl, nw, interleave, cost; } shapes[] = {
+                {32, 128, 8, 0, 81}, {32, 128, 4, 0, 50}, {32, 64, 8, 1, 48}, {32, 64, 4, 0, 31}};
+            int64_t best = -1;
+            for (const auto &t : shapes) {
+                const int tn = t.wn * t.nw;
+                const int64_t c = (int64_t)((pl->Ns + tn - 1) / tn) * ((pl->L + t.tl - 1) / t.tl) * t.cost;
+                if (best >= 0 && c >= best) continue;
+                best = c;
+                pl->wn = t.wn;
+                pl->tl = t.tl;
+                pl->nw = t.nw;
+                pl->interleave = t.interleave;
+            }
         } else {
-            tl = 64;
-            nw = 4;
-            wn = pl->Ns > 128 ? 64 : 32;
+            // Sample by sample: TL columns (l), NW waves of WN rows (n).
+            //   L > 64: 128 columns; 8 waves x 32 rows (two waves per SIMD) when
+            //           Ns > 128, else 4 waves x 32 rows
+            //   L <= 64: 64 columns; 4 waves x 64 rows (Ns > 128) or x 32 rows
+            pl->tl = pl->L > 64 ? 128 : 64;
+            pl->nw = pl->L > 64 && pl->Ns > 128 ? 8 : 4;
+            pl->wn = pl->L <= 64 && pl->Ns > 128 ? 64 : 32;
+            pl->interleave = 0;
         }
-        pl->wn = wn;
-        pl->tl = tl;
-        pl->nw = nw;
-        pl->interleave = 0;
-        pl->tn = nw * wn;
+        pl->tn = pl->nw * pl->wn;
         pl->items_target = pl->ncu;
         pl->min_chunk = 1024;
         pl->occupancy = 1;

@@ -21,6 +21,7 @@ struct rs_plan {
     int nw = 4;                     // waves per workgroup (MFMA)
     int interleave = 0;             // MFMA, NW = 8: 1 = software-pipelined schedule, 0 = phase-shifted waves
     int n_tiles = 0, l_tiles = 0;
+    int mirror = 0;                 // MFMA: the kernel on mirrored sample pairs (complex64 plans)
     int64_t items_target = 0;       // work items aimed at for one cube
     int min_chunk = 0;              // smallest pixel chunk
     int occupancy = 1;              // resident workgroups per CU of the main kernel

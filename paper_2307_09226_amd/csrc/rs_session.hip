@@ -44,7 +44,7 @@ int64_t now_ns()
 
 constexpr int kRing = 3;         // job-table slots (at most 2 slices in flight)
 constexpr int kMaxVariants = 8;  // job entries per request and slot: room for scale, main and reduce jobs
-constexpr int kMaxGroups = 16;   // tile configurations per slice (the library builds 11)
+constexpr int kMaxGroups = 24;   // tile configurations per slice (the library builds 11 for each of two kernels)
 constexpr int kSide = 3;         // streams on which a slice's configurations run side by side
 
 struct ring_slot {
@@ -133,7 +133,7 @@ hipError_t enqueue_slice(rs_session *s, ring_slot &rg, const rs_sched::Slice &sl
         bool found = false;
         for (auto &g : groups)
             if (g.wn == p.r->plan->wn && g.tl == p.r->plan->tl && g.nw == p.r->plan->nw &&
-                g.il == p.r->plan->interleave)
+                g.il == p.r->plan->interleave && g.pl->mirror == p.r->plan->mirror)
                 found = true;
         if (!found)
             groups.push_back(group{p.r->plan->wn, p.r->plan->tl, p.r->plan->nw, p.r->plan->interleave, 0, 0, 0,
@@ -143,7 +143,7 @@ hipError_t enqueue_slice(rs_session *s, ring_slot &rg, const rs_sched::Slice &sl
         g.j0 = nj;
         for (const auto &p : parts) {
             if (p.r->plan->wn != g.wn || p.r->plan->tl != g.tl || p.r->plan->nw != g.nw ||
-                p.r->plan->interleave != g.il)
+                p.r->plan->interleave != g.il || p.r->plan->mirror != g.pl->mirror)
                 continue;
             rs_job j = session_job(s, p.r);
             j.item_begin = g.items;
