@@ -29,9 +29,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "scatterer-sample terms/s (P*M*N*Ns*L/s) MFMA vs FP64-direct at stated err; p50/p99"
 PEAK_FP16 = 2.5e15     # dense fp16 matrix flop/s, MI355X
-PEAK_FP64 = 78.6e12    # fp64 vector flop/s, MI355X
+PEAK_FP64 = 78.6e12    # fp64 matrix (and vector) flop/s, MI355X
 FLOP_MFMA = 12         # 3 split products x 2 real MACs (a mirrored sample pair shares 4) x 2
-FLOP_PLAIN = 8         # one binary64 complex MAC
+FLOP_PLAIN = 4         # 2 binary64 real MACs (a mirrored sample pair shares 4)
 
 # HBM bytes per launch of k_mfma_mirror on the headline frame: rocprofv3 --pmc
 # FETCH_SIZE and WRITE_SIZE (KiB per dispatch) scaled by what the same counters
@@ -39,8 +39,8 @@ FLOP_PLAIN = 8         # one binary64 complex MAC
 # the kernel sources they were taken on; any change to those sources turns
 # the figure into null until the counters are taken again.
 TRAFFIC = {"sources": ("rs_mirror.hip", "rs_device.h", "rs_internal.h", "rs_split16.h"),
-           "sources_sha256": "ee697c0f19235eea98052e24ba53d14bd2656c22d9740b96fde914d0ade32ab0",
-           "fetch_bytes": 2.0 * 7251 * 1024, "write_bytes": 71064 * 1024}
+           "sources_sha256": "6e9b24fa56a2fa023ae20047286c2e82fb44d1d0df3a7df43d2f0425f9c5ee14",
+           "fetch_bytes": 2.0 * 6873 * 1024, "write_bytes": 71064 * 1024}
 # The same for one rs_range_doppler_ws call on the 100-frame walk (k_rd_fused,
 # k_rd_merge, k_rd_peak summed).
 RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_fft.h"),
@@ -293,7 +293,7 @@ def main():
         out["plain_fp64"] = {
             "terms_per_s": terms / (pwall / P_STEPS), "ms_per_step": pwall * 1e3 / P_STEPS,
             "p50_ms": pct(pper, 50), "p99_ms": pct(pper, 99), "kernel_ms": pk_avg,
-            "roofline": {"bound": "fp64 vector", "achieved": FLOP_PLAIN * terms / (pk_avg * 1e-3) / 1e12,
+            "roofline": {"bound": "fp64 matrix", "achieved": FLOP_PLAIN * terms / (pk_avg * 1e-3) / 1e12,
                          "peak": PEAK_FP64 / 1e12, "unit": "TFLOP/s",
                          "frac": FLOP_PLAIN * terms / (pk_avg * 1e-3) / PEAK_FP64},
             "parity": parity_sampled(radar, px, pcube.cpu().numpy()),

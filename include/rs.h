@@ -25,8 +25,10 @@
  * available as a variant (rs_model_flags).
  *
  * Two forms compute Y:
- *   RS_FORM_FP64_DIRECT   binary64 phasors and binary64 complex
- *                         multiply-accumulate on the vector ALUs;
+ *   RS_FORM_FP64_DIRECT   binary64 phasors and binary64 multiply-accumulate
+ *                         on the binary64 matrix instruction, fast time
+ *                         taken from its middle (mirrored samples share
+ *                         their cosine and sine sums);
  *   RS_FORM_MFMA_SPLIT16  binary64 phase arguments reduced mod 1, binary32
  *                         phasors split into hi + lo binary16 parts, and the
  *                         per-channel complex contraction

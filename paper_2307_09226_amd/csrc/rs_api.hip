@@ -45,7 +45,12 @@ rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *ch
         *chunk = pl->min_chunk;
         return RS_OK;
     }
-    const int64_t tiles = (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
+    // plain form: chunks for items_target tiles of 64 samples x 64 or 128
+    // blocks whatever the kernel's tile is, so that the workspace of a call
+    // does not depend on it
+    const int64_t tiles = pl->form == RS_FORM_FP64_DIRECT
+                              ? (int64_t)pl->C * ((pl->Ns + 63) / 64) * (pl->L <= 64 ? 1 : (pl->L + 127) / 128)
+                              : (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
     int64_t s_target = pl->items_target / tiles;
     if (s_target < 1) s_target = 1;
     int64_t ch = (P + s_target - 1) / s_target;
@@ -53,6 +58,24 @@ rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *ch
     // steps in pairs)
     ch = round_up(ch, pl->mirror ? 64 : 16);
     if (ch < pl->min_chunk) ch = pl->min_chunk;
+    // Few pixels: where the smallest chunk leaves compute units without a
+    // work item, finer chunks (whole steps), as long as the partial sums stay
+    // within 16 MiB.  1 x 4, Ns 128, L 64, 4,057 pixels: 38 us with 4 chunks of
+    // 1,024, 20.5 us with 16 of 256, 20.6 us with 32 of 128, 25.4 us with 64
+    // of 64 (the reduction grows); plain form, 2 x 4, 64 x 32, 4,096 pixels: 31.6 us with chunks of
+    // 256, 28.7 us with 128 (256 work items).
+    const int64_t fine = pl->mirror ? 256 : (pl->form == RS_FORM_FP64_DIRECT ? 64 : 0);
+    const int64_t items = (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
+    if (fine > 0 && (P + ch - 1) / ch * items < pl->ncu) {
+        const int64_t cube = (int64_t)pl->C * pl->L * pl->Ns * (pl->mirror ? 8 : 16);
+        int64_t s2 = pl->ncu / items;
+        if (s2 > ((int64_t)16 << 20) / cube) s2 = ((int64_t)16 << 20) / cube;
+        if (s2 >= 1) {
+            int64_t c2 = round_up((P + s2 - 1) / s2, pl->mirror ? 64 : 16);
+            if (c2 < fine) c2 = fine;
+            if (c2 < ch) ch = c2;
+        }
+    }
     if (ch > (int64_t)1 << 30) return rs_fail(RS_E_INVALID, "pixel count too large");
     *chunk = (int32_t)ch;
     *S = (int32_t)((P + ch - 1) / ch);
@@ -222,7 +245,7 @@ rs_status rs_launch_main(const rs_plan *pl, const rs_launch &L, bool block_stren
     if (L.total <= 0) return RS_OK;
     const bool timed = rs_timer_begin(st);
     if (pl->form == RS_FORM_FP64_DIRECT)
-        rs_launch_plain(L, pl->tl, grid, st);
+        rs_launch_plain(L, pl->tn, pl->tl, grid, st);
     else if (pl->mirror)
         rs_launch_mirror(L, pl->wn, pl->tl, pl->nw, pl->interleave != 0, block_strength, grid, st);
     else
@@ -385,12 +408,24 @@ static rs_status plan_common(const rs_radar *r, rs_form form, rs_dtype dtype, in
 void rs_choose_tiles(rs_plan *pl)
 {
     if (pl->form == RS_FORM_FP64_DIRECT) {
-        pl->tn = 64;
-        pl->tl = pl->L <= 64 ? 64 : 128;
+        // Tiles of tn samples x tl blocks: the one that covers Ns x L in the
+        // least time.  cost: relative time per pixel and work item of a full
+        // launch (3 x 4, 256 x 128, 65,536 pixels: 128x128 1.71 ms, 128x64 1.98
+        // ms, 64x32 2.68 ms; 256 x 32, 30,000 pixels: 0.79, 0.46, 0.33 ms).
+        static const struct { int tn, tl, nw, cost; } shapes[] = {{128, 128, 8, 279}, {128, 64, 8, 165}, {64, 32, 4, 58}};
+        int64_t best = -1;
+        for (const auto &t : shapes) {
+            const int64_t c = (int64_t)((pl->Ns + t.tn - 1) / t.tn) * ((pl->L + t.tl - 1) / t.tl) * t.cost;
+            if (best >= 0 && c >= best) continue;
+            best = c;
+            pl->tn = t.tn;
+            pl->tl = t.tl;
+            pl->nw = t.nw;
+        }
         pl->wn = 0;
         pl->items_target = (int64_t)pl->ncu * 4;
         pl->min_chunk = 256;
-        pl->occupancy = 2;
+        pl->occupancy = pl->nw == 4 ? 2 : 1;
     } else {
         if (pl->mirror) {
             // Mirrored pairs: tiles of NW*WN samples (n) x TL blocks (l): the shape
@@ -486,7 +521,7 @@ extern "C" rs_status rs_plan_describe(const rs_plan *pl, int64_t P, char *buf, s
              "\"model\": %d}",
              pl->form == RS_FORM_FP64_DIRECT ? "fp64_direct" : "mfma_split16",
              pl->dtype == RS_C128 ? "complex128" : "complex64", pl->C, pl->Ns, pl->L, pl->tn,
-             pl->tl, pl->wn, pl->form == RS_FORM_FP64_DIRECT ? 4 : pl->nw, pl->n_tiles, pl->l_tiles,
+             pl->tl, pl->wn, pl->nw, pl->n_tiles, pl->l_tiles,
              pl->form == RS_FORM_FP64_DIRECT ? "lds_blocks"
                                               : (pl->nw == 8 && !pl->interleave ? "phase_shifted" : "pipelined"),
              S, chunk, (long long)S * pl->C * pl->n_tiles * pl->l_tiles, pl->ncu, pl->model);

@@ -16,6 +16,7 @@ __global__ __launch_bounds__(256) void k_reduce(rs_launch Lc)
     const int64_t cln = (int64_t)(J.M * J.N) * J.L * J.Ns;
     const PT *p = reinterpret_cast<const PT *>(J.partial) + idx;
     double re = 0.0, im = 0.0;
+#pragma unroll 4
     for (int s = 0; s < J.S; ++s) {
         const PT v = p[(int64_t)s * cln];
         re += (double)v.x;
