@@ -44,8 +44,8 @@ TRAFFIC = {"sources": ("rs_mirror.hip", "rs_device.h", "rs_internal.h", "rs_spli
 # The same for one rs_range_doppler_ws call on the 100-frame walk (k_rd_fused,
 # k_rd_merge, k_rd_peak summed).
 RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_fft.h"),
-              "sources_sha256": "95099bdcdb4bfc8754d0a938c3fa665fedb0f6060603a9d34e880fcf3a09d309",
-              "fetch_bytes": 2.0 * (158861 + 20530 + 52) * 1024, "write_bytes": (42880 + 12825 + 55) * 1024}
+              "sources_sha256": "e69755b3be11e6fa24bfe29d4e6f0d7229154507f0cbfa6ba48f29b1a002b4ba",
+              "fetch_bytes": 2.0 * (158860 + 20534 + 52) * 1024, "write_bytes": (42880 + 12825 + 55) * 1024}
 
 
 # VALU wave-instructions per launch of k_render on the 100-frame walk

@@ -471,11 +471,13 @@ typedef struct {
  *   doppler_time  float32 [nframes][L]      power[k_peak][.] of each frame:
  *                                           its velocity spectrum at the peak
  *   peaks         rs_rd_peak [nframes]
- * Arithmetic in float32 with twiddles from binary64: for Ns = 256 and
- * L in 16..128 each channel's 2-D FFT runs in registers and LDS within one
- * workgroup and the channels' power is summed in registers (partial maps
- * of the workgroups that share a frame are added in a fixed order); other
- * shapes take two passes of radix-2 LDS FFTs.  Deterministic.
+ * Arithmetic in float32 with twiddles from binary64.  Many frames with
+ * Ns = 256 and L = 64 or 128: each channel's 2-D FFT runs in registers and LDS
+ * within one workgroup and the channels' power is summed in registers
+ * (partial maps of the workgroups that share a frame are added in a fixed
+ * order); otherwise a fast-time pass into the workspace and a slow-time pass
+ * over runs of channels, whose partial maps are added in a fixed order.
+ * Deterministic.
  * Needs Ns and L powers of two, Ns <= 4096, L <= 1024 (else
  * RS_E_UNSUPPORTED).  Temporary device memory
  * (rs_range_doppler_workspace_bytes) is allocated and freed in stream

@@ -172,10 +172,9 @@ rs_status rs_check_pixels(const rs_plan *pl, const rs_pixels *px)
 // Workspaces come from a pool of the plan, not the device's: the device's
 // pool hands its memory back at every synchronisation, and mapping 2 MiB or
 // more again costs a call 60-90 us (4,057-pixel request, waited for: 99 ->
-// 37 us; the
-// 65,536-pixel NUFFT frame 197 -> 119 us).  A plan's pool keeps
-// at most kPoolKeep bytes between calls and goes with the plan.  A stream
-// under capture takes the device's pool as before.
+// 37 us; the 65,536-pixel NUFFT frame: 197 -> 119 us).  A plan's pool keeps at
+// most kPoolKeep bytes between calls and goes with the plan.  A stream under
+// capture takes the device's pool as before.
 constexpr uint64_t kPoolKeep = (uint64_t)256 << 20;
 
 static void pool_create(rs_plan *pl)

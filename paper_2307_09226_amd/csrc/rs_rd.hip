@@ -6,7 +6,8 @@
 //   X_c[k][d] = sum_l sum_n Y[c][l][n] exp(-j2pi k n / Ns) exp(+j2pi d l / L)
 //   power[k][d] = sum_c |X_c[k][d]|^2
 //
-// Fused path (Ns = 256, L = 16 D2 with D2 in {1, 2, 4, 8}): one workgroup
+// Fused path (Ns = 256, L = 16 D2 with D2 in {4, 8}, many frames: see
+// rd_fused_pays): one workgroup
 // holds a whole channel's L x 256 tile in registers, 64 entries a thread
 // (4 rows of 16), and takes it through both FFTs without touching HBM in
 // between:
@@ -28,15 +29,26 @@
 // frame) written and read back, plus the map.
 //
 // Two-pass path (other shapes):
-//   k_range_fft      fast-time FFT of every (frame, channel, block) row in
-//                    LDS -> rf[F][C][L][Ns] (float2 workspace)
-//   k_doppler_power  per (frame, group of KB range bins): for each channel
-//                    the inverse-sign FFT over blocks in LDS, |.|^2 summed in
-//                    registers -> power[F][Ns][L]; plus the group's maximum
+//   k_range_reg      fast-time FFT of every (frame, channel, block) row in
+//                    registers (16 points a thread, 16 x 16 x M factors,
+//                    exchanged through LDS inside one wavefront) ->
+//                    rf[F][C][L][Ns] (float2 workspace); Ns 16..1024
+//   k_doppler_reg    per (frame, group of range bins, run of channels): the
+//                    inverse-sign FFT over blocks as 16 x M in registers and
+//                    one LDS exchange, |.|^2 summed in registers over the
+//                    run -> one partial map per run; L 16..256
+//   k_map_merge      the runs' partial maps summed in run order -> power,
+//                    and the block maxima
 //   k_rd_peak        as above
-// The LDS FFTs are iterative radix-2 (decimation in time, bit-reversed
-// load).  Both paths compute in float32 with twiddles evaluated in binary64;
-// both are deterministic (fixed operation and summation order).
+// The runs fill the chip: one 192-channel cube of 512 x 64 has 8 groups of
+// range bins, so a workgroup per group that loops over all channels used 8
+// to 32 of 256 compute units (0.577 ms; 0.044 ms in runs).
+//   k_range_fft, k_doppler_power   the same two passes for the remaining
+//                    lengths (Ns < 16 or > 1024, L < 16 or > 256): iterative
+//                    radix-2 FFTs in LDS, a workgroup per row group and per
+//                    group of range bins
+// All paths compute in float32 with twiddles evaluated in binary64 and are
+// deterministic (fixed operation and summation order).
 #include "rs_api_internal.h"
 #include "rs_fft.h"
 
@@ -47,6 +59,11 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxPerThread = 16;   // power elements per thread in k_doppler_power
 constexpr int kGroupElems = 4096;   // KB * L, at most (dynamic LDS <= 64 KiB)
+// k_range_reg workgroups per compute unit (192 channels of 512 x 64: 44.0 us a
+// call with 2, 45.3 with 4, 50.5 with 8; 10 frames of 8 x 1024 x 64: 42.3, 46.9,
+// 46.6), and k_doppler_reg workgroups per compute unit aimed at (192 channels
+// of 512 x 256: 131 us with 1, 126 with 2, 133 with 4)
+constexpr int kRangePerCu = 2, kDopplerPerCu = 2;
 
 struct rd_peak_part {
     float v;
@@ -167,6 +184,7 @@ constexpr int kFR = 16;                   // 256 = 16 x 16
 constexpr int kFHalf = kFNs / 2;          // range bins per slow-time half
 constexpr int kFX1 = kFR * (kFR + 1);     // one row of the fast-time transpose (padded, = 16 mod 32)
 constexpr int kMergeCells = 4096;         // cells per k_rd_merge workgroup (256 threads, 4 float4 each)
+constexpr int kMapCells = 256;            // cells per k_map_merge workgroup
 constexpr int kFusedRows = 4;             // tile rows a thread holds (64 entries)
 
 // cos(2 pi m / 16), m taken modulo 16
@@ -238,6 +256,196 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---------------------------------------------------------------------------
+// Two-pass path in registers
+// ---------------------------------------------------------------------------
+
+// exp(sign j 2 pi num / den), evaluated in binary64
+__device__ __forceinline__ float2 twiddle(int num, int den, double sign)
+{
+    double sn, cs;
+    sincospi(2.0 * (double)num / (double)den, &sn, &cs);
+    return make_float2((float)cs, (float)(sign * sn));
+}
+
+template <int LOGN>
+struct range_shape {
+    static constexpr int N = 1 << LOGN, T = N / 16;   // row length, threads per row (16 points each)
+    static constexpr int M2 = T > 16 ? T / 16 : 1;     // last factor of a three-factor row
+    static constexpr int ROWS = kThreads / T;          // rows per workgroup
+    // LDS of a row: the transpose [k1][q] with an odd stride, then (three
+    // factors) [k2a][q0][k1] with 16 slots of padding per k2a
+    static constexpr int X = T > 16 ? 16 * (T + 16) : 16 * (T + 1);
+    static_assert(LOGN >= 4 && LOGN <= 10, "one wavefront holds a row");
+};
+
+// Fast-time FFT, row by row: n = q + T n1, 16-point DFT over n1 -> k1, times
+// exp(-j 2 pi q k1 / N), then over q: T points (T <= 16), k = k1 + 16 k2; or
+// 16 x M2 points (q = q0 + M2 q1; over q1 -> k2a, times exp(-j 2 pi q0 k2a / T),
+// over q0 -> k2b), k = k1 + 16 (k2a + 16 k2b).  A workgroup strides over the
+// rows with its twiddles in registers and loads its next rows under the
+// current ones.  Memory bound: 192 x 64 rows of 512 (50 MB in, 50 MB out)
+// 34.8 us as radix-2 passes through LDS, 22 us here (4.6 TB/s).
+template <int LOGN, typename IT>
+__global__ __launch_bounds__(kThreads) void k_range_reg(const IT *__restrict__ cubes, float2 *__restrict__ rf,
+                                                        int64_t rows_total)
+{
+    using S = range_shape<LOGN>;
+    constexpr int N = S::N, T = S::T, M2 = S::M2, ROWS = S::ROWS;
+    __shared__ float2 sx[ROWS * S::X];
+    const int t = threadIdx.x % T, lr = threadIdx.x / T;
+    float2 *x = sx + lr * S::X;
+    const int k1t = t & 15, q0t = t >> 4;   // three factors: this thread's k1 and q0
+    float2 tw1[16], tw2[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        tw1[k] = twiddle((t * k) & (N - 1), N, -1.0);
+        tw2[k] = M2 > 1 ? twiddle((q0t * k) & (T - 1), T, -1.0) : make_float2(1.f, 0.f);
+    }
+    const int64_t ngroups = (rows_total + ROWS - 1) / ROWS;
+    float2 v[16];
+    auto load = [&](int64_t g) {
+        const int64_t row = min(g * ROWS + lr, rows_total - 1);
+        const IT *src = cubes + row * N + t;
+#pragma unroll
+        for (int n1 = 0; n1 < 16; ++n1) v[n1] = load_c(src + T * n1);
+    };
+    int64_t g = blockIdx.x;
+    if (g < ngroups) load(g);
+    for (; g < ngroups; g += gridDim.x) {
+        const int64_t row = g * ROWS + lr;
+        const bool in = row < rows_total;
+        float2 *dst = rf + min(row, rows_total - 1) * N;
+        dft_reg<16, -1>(v);
+        x[t] = v[0];
+#pragma unroll
+        for (int k1 = 1; k1 < 16; ++k1) x[k1 * (T + 1) + t] = cmul(v[k1], tw1[k1]);
+        wave_sync();
+        float2 z[16];
+        if constexpr (M2 == 1) {
+            constexpr int E = 16 / T;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+#pragma unroll
+                for (int q = 0; q < T; ++q) z[e * T + q] = x[(t + T * e) * (T + 1) + q];
+            wave_sync();
+            if (g + gridDim.x < ngroups) load(g + gridDim.x);
+#pragma unroll
+            for (int e = 0; e < E; ++e) dft_reg<T, -1>(z + e * T);
+            if (in) {
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+#pragma unroll
+                    for (int k2 = 0; k2 < T; ++k2) dst[t + T * e + 16 * k2] = z[e * T + k2];
+            }
+        } else {
+            constexpr int E = 16 / M2, YS = 16 * M2 + 16;
+#pragma unroll
+            for (int q1 = 0; q1 < 16; ++q1) z[q1] = x[k1t * (T + 1) + q0t + M2 * q1];
+            wave_sync();
+            dft_reg<16, -1>(z);
+#pragma unroll
+            for (int k2a = 0; k2a < 16; ++k2a) x[k2a * YS + q0t * 16 + k1t] = cmul(z[k2a], tw2[k2a]);
+            wave_sync();
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+#pragma unroll
+                for (int q0 = 0; q0 < M2; ++q0) z[e * M2 + q0] = x[(q0t + M2 * e) * YS + q0 * 16 + k1t];
+            wave_sync();
+            if (g + gridDim.x < ngroups) load(g + gridDim.x);
+#pragma unroll
+            for (int e = 0; e < E; ++e) dft_reg<M2, -1>(z + e * M2);
+            if (in) {
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+#pragma unroll
+                    for (int k2b = 0; k2b < M2; ++k2b) dst[k1t + 16 * (q0t + M2 * e + 16 * k2b)] = z[e * M2 + k2b];
+            }
+        }
+    }
+}
+
+// Slow-time FFT and power of a group of KB range bins over a run of channels.
+// Thread (cp, j, k): range bin k, blocks l = j + M l1; 16-point inverse-sign
+// DFT over l1 -> d1, times exp(+j 2 pi j d1 / L), exchanged through LDS, then
+// the M-point DFT over j for d1 = (16 / M) j + e; cells d = d1 + 16 d2.  Where
+// Ns leaves threads over, cp runs side by side.  Run s of S covers channels
+// [s per, (s + 1) per) and writes slots[f S + s][k][d].  The next channel is
+// loaded under the current one's exchange.
+template <int M>
+__global__ __launch_bounds__(kThreads) void k_doppler_reg(const float2 *__restrict__ rf, float *__restrict__ slots,
+                                                          int C, int Ns, int logkb, int S, int per)
+{
+    constexpr int L = 16 * M, E = 16 / M;
+    constexpr int LOGM = M >= 16 ? 4 : M >= 8 ? 3 : M >= 4 ? 2 : M >= 2 ? 1 : 0;
+    // exchange: (cp, d1, j, k) at cp CPS + d1 DS + j KB + k; the pad puts
+    // neighbouring d1 of 16 range bins in the other half of the banks
+    __shared__ float2 ex[kThreads * 16 + 16 * 16];
+    const int KB = 1 << logkb, CP = kThreads >> (logkb + LOGM);
+    const int DS = M * KB + (M == 16 ? 16 : 0), CPS = 16 * DS;   // CP CPS <= the array (M = 16: CP = 1)
+    const int tid = threadIdx.x;
+    const int k = tid & (KB - 1), j = (tid >> logkb) & (M - 1), cp = tid >> (logkb + LOGM);
+    const int groups = Ns >> logkb, sblk = S / CP;
+    const int s = (int)(blockIdx.x % sblk) * CP + cp;
+    const int fg = (int)(blockIdx.x / sblk);
+    const int f = fg / groups, k0 = (fg % groups) << logkb;
+    float2 tw[16];
+#pragma unroll
+    for (int d = 0; d < 16; ++d) tw[d] = twiddle((j * d) & (L - 1), L, +1.0);
+    float acc[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    const int c0 = s * per, c1 = min(C, c0 + per);
+    float2 u[16];
+    auto load = [&](int c) {
+        const float2 *src = rf + (((int64_t)f * C + min(c, C - 1)) * L + j) * Ns + k0 + k;
+#pragma unroll
+        for (int l1 = 0; l1 < 16; ++l1) u[l1] = src[(int64_t)(M * l1) * Ns];
+    };
+    load(c0);
+    for (int i = 0; i < per; ++i) {
+        const bool in = c0 + i < c1;
+        dft_reg<16, +1>(u);
+        float2 z[16];
+        if constexpr (M == 1) {
+#pragma unroll
+            for (int d = 0; d < 16; ++d) z[d] = u[d];
+            if (i + 1 < per) load(c0 + i + 1);
+        } else {
+            float2 *w = ex + cp * CPS + j * KB + k;
+            w[0] = u[0];
+#pragma unroll
+            for (int d1 = 1; d1 < 16; ++d1) w[d1 * DS] = cmul(u[d1], tw[d1]);
+            if (i + 1 < per) load(c0 + i + 1);
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+#pragma unroll
+                for (int jj = 0; jj < M; ++jj) z[e * M + jj] = ex[cp * CPS + (E * j + e) * DS + jj * KB + k];
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < E; ++e) dft_reg<M, +1>(z + e * M);
+        }
+#pragma unroll
+        for (int d = 0; d < 16; ++d)
+            acc[d] = in ? __builtin_fmaf(z[d].x, z[d].x, __builtin_fmaf(z[d].y, z[d].y, acc[d])) : acc[d];
+    }
+    // through LDS into the map's order
+    float *sm = reinterpret_cast<float *>(ex) + cp * (KB * (L + 1));
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int d2 = 0; d2 < M; ++d2) sm[k * (L + 1) + E * j + e + 16 * d2] = acc[e * M + d2];
+    __syncthreads();
+    const int lt = tid & (M * KB - 1);
+    float *dst = slots + (((int64_t)f * S + s) * Ns + k0) * L;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int e = lt + i * M * KB;
+        dst[e] = sm[(e / L) * (L + 1) + e % L];
+    }
 }
 
 template <int D2, int RPT>
@@ -431,9 +639,54 @@ __global__ __launch_bounds__((rd_fused_shape<D2, RPT>::T)) void k_rd_fused(const
     }
 }
 
+// The largest of 256 threads' (best, index) pairs (smallest index on ties, -1:
+// none) to *part.
+__device__ __forceinline__ void block_peak(float best, int bidx, rd_peak_part *part)
+{
+    __shared__ float rv[256];
+    __shared__ int ri[256];
+    rv[threadIdx.x] = best;
+    ri[threadIdx.x] = bidx;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (threadIdx.x < o) {
+            const float v2 = rv[threadIdx.x + o];
+            const int i2 = ri[threadIdx.x + o];
+            if (i2 >= 0 && (ri[threadIdx.x] < 0 || v2 > rv[threadIdx.x] ||
+                            (v2 == rv[threadIdx.x] && i2 < ri[threadIdx.x]))) {
+                rv[threadIdx.x] = v2;
+                ri[threadIdx.x] = i2;
+            }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        rd_peak_part p;
+        p.v = rv[0];
+        p.idx = ri[0];
+        *part = p;
+    }
+}
+
+// Stores four neighbouring cells of a map and takes them into the running
+// maximum (d = 0 skipped when skip_static).
+__device__ __forceinline__ void store_cells(float *map, int e, const float4 &s, int L, int skip_static, float &best,
+                                            int &bidx)
+{
+    *reinterpret_cast<float4 *>(map + e) = s;
+    const float vals[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = e + i;
+        if (!(skip_static && (c & (L - 1)) == 0) && vals[i] > best) {
+            best = vals[i];
+            bidx = c;
+        }
+    }
+}
+
 // Per (frame, block of 4096 cells): the frame's partial maps summed in
-// workgroup order -> power, and the block's maximum (smallest cell index on
-// ties; d = 0 skipped when skip_static).
+// workgroup order -> power, and the block's maximum.
 __global__ __launch_bounds__(256) void k_rd_merge(const float *__restrict__ slots, float *__restrict__ power,
                                                  rd_peak_part *parts, int C, int64_t nitems, int W, int J,
                                                  int cells, int L, int skip_static)
@@ -461,42 +714,52 @@ __global__ __launch_bounds__(256) void k_rd_merge(const float *__restrict__ slot
     float best = -1.f;
     int bidx = -1;
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int e = b * kMergeCells + v * 1024 + threadIdx.x * 4;
-        *reinterpret_cast<float4 *>(power + f * (int64_t)cells + e) = s[v];
-        const float vals[4] = {s[v].x, s[v].y, s[v].z, s[v].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = e + i;
-            if (!(skip_static && (c & (L - 1)) == 0) && vals[i] > best) {
-                best = vals[i];
-                bidx = c;
-            }
-        }
+    for (int v = 0; v < V; ++v)
+        store_cells(power + f * (int64_t)cells, b * kMergeCells + v * 1024 + threadIdx.x * 4, s[v], L, skip_static, best,
+                    bidx);
+    block_peak(best, bidx, parts + blockIdx.x);
+}
+
+// The same for the two-pass path: per (frame, block of kMapCells cells) the S
+// partial maps of the frame, four quarters of them by 64 threads each (a
+// single map has few blocks, and its sum is a chain of S loads: 21.9 us for
+// 64 partial maps of 512 x 64 with one thread per cell), the quarters added in
+// order.
+__global__ __launch_bounds__(256) void k_map_merge(const float *slots, float *power, rd_peak_part *parts, int S,
+                                                   int nblk, int cells, int L, int skip_static)
+{
+    __shared__ float4 part[4][kMapCells / 4];
+    const int64_t f = blockIdx.x / nblk;
+    const int b = blockIdx.x % nblk;
+    const int q = threadIdx.x >> 6, i = threadIdx.x & 63;
+    const int e = b * kMapCells + i * 4;
+    const int s0 = S * q / 4, s1 = S * (q + 1) / 4;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float *src = slots + f * S * (int64_t)cells + e;
+#pragma unroll 8
+    for (int k = s0; k < s1; ++k) {
+        const float4 p = *reinterpret_cast<const float4 *>(src + (int64_t)k * cells);
+        s.x += p.x;
+        s.y += p.y;
+        s.z += p.z;
+        s.w += p.w;
     }
-    __shared__ float rv[256];
-    __shared__ int ri[256];
-    rv[threadIdx.x] = best;
-    ri[threadIdx.x] = bidx;
+    part[q][i] = s;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            const float v2 = rv[threadIdx.x + o];
-            const int i2 = ri[threadIdx.x + o];
-            if (i2 >= 0 && (ri[threadIdx.x] < 0 || v2 > rv[threadIdx.x] ||
-                            (v2 == rv[threadIdx.x] && i2 < ri[threadIdx.x]))) {
-                rv[threadIdx.x] = v2;
-                ri[threadIdx.x] = i2;
-            }
+    float best = -1.f;
+    int bidx = -1;
+    if (q == 0) {
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            const float4 p = part[k][i];
+            s.x += p.x;
+            s.y += p.y;
+            s.z += p.z;
+            s.w += p.w;
         }
-        __syncthreads();
+        store_cells(power + f * (int64_t)cells, e, s, L, skip_static, best, bidx);
     }
-    if (threadIdx.x == 0) {
-        rd_peak_part p;
-        p.v = rv[0];
-        p.idx = ri[0];
-        parts[blockIdx.x] = p;
-    }
+    block_peak(best, bidx, parts + blockIdx.x);
 }
 
 // Per frame: maximum over the groups (smallest index on ties), the peak
@@ -572,6 +835,35 @@ int64_t rd_fused_workgroups(int64_t nframes, int C, int ncu)
     return std::max<int64_t>(1, (n + per - 1) / per);
 }
 
+template <typename IT>
+void launch_range_reg(int logn, const void *cubes, float2 *rf, int64_t rows, int ncu, hipStream_t st)
+{
+    const IT *src = reinterpret_cast<const IT *>(cubes);
+    const int64_t groups = (rows * (int64_t)((1 << logn) / 16) + kThreads - 1) / kThreads;
+    const dim3 grid((unsigned)std::min<int64_t>(groups, (int64_t)ncu * kRangePerCu));
+    switch (logn) {
+    case 4: hipLaunchKernelGGL((k_range_reg<4, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    case 5: hipLaunchKernelGGL((k_range_reg<5, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    case 6: hipLaunchKernelGGL((k_range_reg<6, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    case 7: hipLaunchKernelGGL((k_range_reg<7, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    case 8: hipLaunchKernelGGL((k_range_reg<8, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    case 9: hipLaunchKernelGGL((k_range_reg<9, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    default: hipLaunchKernelGGL((k_range_reg<10, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
+    }
+}
+
+void launch_doppler_reg(int L, const float2 *rf, float *slots, int C, int Ns, int logkb, int S, int per, unsigned grid,
+                        hipStream_t st)
+{
+    switch (L) {
+    case 16: hipLaunchKernelGGL(k_doppler_reg<1>, dim3(grid), dim3(kThreads), 0, st, rf, slots, C, Ns, logkb, S, per); break;
+    case 32: hipLaunchKernelGGL(k_doppler_reg<2>, dim3(grid), dim3(kThreads), 0, st, rf, slots, C, Ns, logkb, S, per); break;
+    case 64: hipLaunchKernelGGL(k_doppler_reg<4>, dim3(grid), dim3(kThreads), 0, st, rf, slots, C, Ns, logkb, S, per); break;
+    case 128: hipLaunchKernelGGL(k_doppler_reg<8>, dim3(grid), dim3(kThreads), 0, st, rf, slots, C, Ns, logkb, S, per); break;
+    default: hipLaunchKernelGGL(k_doppler_reg<16>, dim3(grid), dim3(kThreads), 0, st, rf, slots, C, Ns, logkb, S, per); break;
+    }
+}
+
 template <int D2, typename IT>
 hipError_t launch_fused(const void *cubes, float *slots, int C, int64_t nitems, int W, int J, hipStream_t st)
 {
@@ -590,12 +882,8 @@ template <typename IT>
 hipError_t launch_fused_l(int L, const void *cubes, float *slots, int C, int64_t nitems, int W, int J,
                           hipStream_t st)
 {
-    switch (L) {
-    case 16: return launch_fused<1, IT>(cubes, slots, C, nitems, W, J, st);
-    case 32: return launch_fused<2, IT>(cubes, slots, C, nitems, W, J, st);
-    case 64: return launch_fused<4, IT>(cubes, slots, C, nitems, W, J, st);
-    default: return launch_fused<8, IT>(cubes, slots, C, nitems, W, J, st);
-    }
+    return L == 64 ? launch_fused<4, IT>(cubes, slots, C, nitems, W, J, st)
+                   : launch_fused<8, IT>(cubes, slots, C, nitems, W, J, st);
 }
 
 }  // namespace
@@ -604,14 +892,30 @@ namespace {
 
 // Workspace of one call, in 256-byte aligned pieces.  Fused path: the
 // partial maps [W][J][cells], the map when the caller wants none, the block
-// maxima.  Two-pass path: the float2 fast-time spectra, the map when the
-// caller wants none, the group maxima.
+// maxima.  Two-pass path: the float2 fast-time spectra, the runs' partial
+// maps [F][S][cells] (L 16..256), the map when the caller wants none, the
+// group maxima.
 struct rd_layout {
     bool fused = false;
     int64_t W = 0, J = 0, nitems = 0;
     int groups = 0, kb = 0;
-    size_t mid = 0, pw = 0, parts = 0, total = 0;   // byte offsets / sizes
+    int S = 0, per = 0, logkb = 0;   // channel runs of k_doppler_reg (S = 0: k_doppler_power)
+    size_t mid = 0, slots = 0, pw = 0, parts = 0, total = 0;   // byte offsets / sizes
 };
+
+// Whether the fused path is the faster one: it reads the cubes once (the
+// two-pass path moves three times the bytes) but runs one workgroup per
+// compute unit, one channel at a time, and merges a partial map per workgroup
+// and frame, so it needs enough (frame, channel, block) rows, and frames of
+// which few workgroups share one.  Measured, fused / two-pass in us (C, L,
+// frames): 12, 128: 1: 33.2 / 20.4, 10: 36.6 / 32.7, 16: 40.5 / 40.7, 32: 57 / 65,
+// 100: 136 / 216; 4, 128: 40: 36 / 42; 8, 64: 32: 31 / 33; 192, 128: 1: 122 / 41,
+// 2: 97 / 62, 4: 106 / 113; 12, 32: 30: 34 / 29; 12, 16: 100: 58 / 34.
+bool rd_fused_pays(int64_t nframes, int C, int Ns, int L)
+{
+    const int64_t rows = nframes * C * L;
+    return Ns == kFNs && L >= 64 && L <= 128 && ((nframes >= 16 && rows >= 16384) || rows >= 98304);
+}
 
 rd_layout rd_plan_layout(const rs_plan *pl, int64_t nframes, bool power_given)
 {
@@ -619,8 +923,8 @@ rd_layout rd_plan_layout(const rs_plan *pl, int64_t nframes, bool power_given)
     rd_layout y;
     const int Ns = pl->Ns, L = pl->L, C = pl->C;
     const int64_t cells = (int64_t)Ns * L;
-    y.fused = Ns == kFNs && L >= 16 && L <= 128;
-    size_t mid_bytes;
+    y.fused = rd_fused_pays(nframes, C, Ns, L);
+    size_t mid_bytes, slot_bytes = 0;
     if (y.fused) {
         y.nitems = nframes * C;
         y.W = rd_fused_workgroups(nframes, C, pl->ncu);
@@ -632,11 +936,27 @@ rd_layout rd_plan_layout(const rs_plan *pl, int64_t nframes, bool power_given)
         y.kb = std::min(std::min(16, kGroupElems / L), Ns);
         y.groups = Ns / y.kb;
         mid_bytes = (size_t)(nframes * C * L * Ns) * sizeof(float2);
+        if (L >= 16 && L <= 256 && Ns >= 16) {
+            // KB range bins x L / 16 threads per channel, CP channels side by
+            // side; enough runs of channels for kDopplerPerCu workgroups per
+            // compute unit
+            const int kb = std::min(Ns, kThreads * 16 / L), cp = kThreads / (kb * (L / 16));
+            y.logkb = __builtin_ctz((unsigned)kb);
+            const int64_t base = nframes * (Ns / kb);
+            int64_t blocks = ((int64_t)pl->ncu * kDopplerPerCu + base - 1) / base;
+            blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, (C + cp - 1) / cp));
+            y.per = (int)((C + blocks * cp - 1) / (blocks * cp));
+            y.S = (int)((C + (int64_t)y.per * cp - 1) / ((int64_t)y.per * cp)) * cp;
+            y.groups = (int)(cells / kMapCells);
+            // one run: its map is the frame's
+            slot_bytes = y.S == 1 ? 0 : (size_t)(nframes * y.S * cells) * sizeof(float);
+        }
     }
     const size_t pw_bytes = power_given ? 0 : (size_t)(nframes * cells) * sizeof(float);
     const size_t part_bytes = (size_t)nframes * y.groups * sizeof(rd_peak_part);
     y.mid = 0;
-    y.pw = up(mid_bytes);
+    y.slots = up(mid_bytes);
+    y.pw = y.slots + up(slot_bytes);
     y.parts = y.pw + up(pw_bytes);
     y.total = y.parts + up(part_bytes);
     return y;
@@ -682,22 +1002,38 @@ rs_status rd_run(const rs_plan *pl, const rd_layout &y, const void *cubes, int32
     } else {
         float2 *rf = reinterpret_cast<float2 *>(ws + y.mid);
         const int64_t rows = (int64_t)nframes * C * L;
-        const int rpw = std::max(1, 2048 / Ns);
-        const int64_t g1 = (rows + rpw - 1) / rpw;
-        const size_t lds1 = (size_t)(Ns / 2 + rpw * Ns) * sizeof(float2);
-        if (pl->dtype == RS_C128)
-            hipLaunchKernelGGL(k_range_fft<double2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
-                               reinterpret_cast<const double2 *>(cubes), rf, rows, logn, rpw);
-        else
-            hipLaunchKernelGGL(k_range_fft<float2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
-                               reinterpret_cast<const float2 *>(cubes), rf, rows, logn, rpw);
+        if (Ns >= 16 && Ns <= 1024) {
+            if (pl->dtype == RS_C128) launch_range_reg<double2>(logn, cubes, rf, rows, pl->ncu, st);
+            else launch_range_reg<float2>(logn, cubes, rf, rows, pl->ncu, st);
+        } else {
+            const int rpw = std::max(1, 2048 / Ns);
+            const int64_t g1 = (rows + rpw - 1) / rpw;
+            const size_t lds1 = (size_t)(Ns / 2 + rpw * Ns) * sizeof(float2);
+            if (pl->dtype == RS_C128)
+                hipLaunchKernelGGL(k_range_fft<double2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
+                                   reinterpret_cast<const double2 *>(cubes), rf, rows, logn, rpw);
+            else
+                hipLaunchKernelGGL(k_range_fft<float2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
+                                   reinterpret_cast<const float2 *>(cubes), rf, rows, logn, rpw);
+        }
         e = hipGetLastError();
         if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "range FFT launch: %s", hipGetErrorString(e));
-        const size_t lds2 = (size_t)(L / 2 + y.kb * L) * sizeof(float2);
-        hipLaunchKernelGGL(k_doppler_power, dim3((unsigned)(nframes * y.groups)), dim3(kThreads), lds2, st, rf, pw,
-                           parts, C, logl, Ns, y.kb, skip_static ? 1 : 0);
+        if (y.S > 0) {
+            float *slots = y.S == 1 ? pw : reinterpret_cast<float *>(ws + y.slots);
+            const int cp = kThreads >> (y.logkb + logl - 4);
+            launch_doppler_reg(L, rf, slots, C, Ns, y.logkb, y.S, y.per,
+                               (unsigned)(nframes * (Ns >> y.logkb) * (int64_t)(y.S / cp)), st);
+            e = hipGetLastError();
+            if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler launch: %s", hipGetErrorString(e));
+            hipLaunchKernelGGL(k_map_merge, dim3((unsigned)(nframes * y.groups)), dim3(256), 0, st, slots, pw, parts, y.S,
+                               y.groups, (int)cells, L, skip_static ? 1 : 0);
+        } else {
+            const size_t lds2 = (size_t)(L / 2 + y.kb * L) * sizeof(float2);
+            hipLaunchKernelGGL(k_doppler_power, dim3((unsigned)(nframes * y.groups)), dim3(kThreads), lds2, st, rf, pw,
+                               parts, C, logl, Ns, y.kb, skip_static ? 1 : 0);
+        }
         e = hipGetLastError();
-        if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler launch: %s", hipGetErrorString(e));
+        if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler map launch: %s", hipGetErrorString(e));
     }
     if (peaks || doppler_time) {
         hipLaunchKernelGGL(k_rd_peak, dim3((unsigned)nframes), dim3(kThreads), 0, st, parts, pw, y.groups, Ns, L, rpb,
@@ -727,7 +1063,7 @@ extern "C" rs_status rs_range_doppler(rs_plan *pl, const void *cubes, int32_t nf
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const rd_layout y = rd_plan_layout(pl, nframes, power != nullptr);
     char *ws = nullptr;
-    if (hipMallocAsync(reinterpret_cast<void **>(&ws), y.total, st) != hipSuccess)
+    if (rs_workspace_alloc(pl, reinterpret_cast<void **>(&ws), y.total, st) != hipSuccess)
         return rs_fail(RS_E_NOMEM, "stream-ordered workspace allocation of %zu bytes failed", y.total);
     rs_status s = rd_run(pl, y, cubes, nframes, skip_static, power, doppler_time, peaks, ws, logn, logl, st);
     const hipError_t e = hipFreeAsync(ws, st);
