@@ -48,13 +48,13 @@ RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_fft.h"),
               "fetch_bytes": 2.0 * (158860 + 20534 + 52) * 1024, "write_bytes": (42880 + 12825 + 55) * 1024}
 
 
-# VALU wave-instructions per launch of k_render on the 100-frame walk
+# VALU wave-instructions per call (four k_render launches) on the 100-frame walk
 # (rocprofv3 --pmc SQ_INSTS_VALU); like the records above, null once its
 # source changes.  The kernel is bound by vector issue (binary64 geometry):
 # 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles per wave64 instruction.
 RENDER_VALU = {"sources": ("rs_scene.hip",),
-               "sources_sha256": "d633d719d222e4f30f07c373dc0120ef798efeae22df77f242c89bcfeabb7333",
-               "valu_instr": 25334220}
+               "sources_sha256": "3ea0eda9dcf6e8ad6a782dfe918e95542714d34fe81ae4964bc7dc02e1c51371",
+               "valu_instr": 13535884}
 PEAK_VALU_ISSUE = 256 * 4 * 2.4e9 / 4
 
 # Offered load of the serving leg, frozen so that latencies stay comparable

@@ -426,7 +426,7 @@ typedef struct {
 } rs_scene;
 
 /* Render `nframes` scenes over one g_az x g_el grid (P = g_az g_el pixels
- * per frame).  scenes: HOST array [nframes] (copied in stream order).
+ * per frame).  scenes: HOST array [nframes] (read before the call returns).
  * noise: device [nframes][P] strength factors (e.g. lognormal draws), or
  * NULL for 1.  x, y, z, amp, vr: device [nframes][P] outputs, frame f at
  * offset f P -- ready for rs_pixels / rs_beat_synthesize_batch.
@@ -506,8 +506,8 @@ rs_status rs_range_doppler_ws(rs_plan *plan, const void *cubes, int32_t nframes,
 /* Per-launch timing of the main (contraction) kernel with HIP events, for
  * profiling.  A timer attached to the calling thread records an event pair
  * around every main-kernel launch made by rs_beat_synthesize* and
- * rs_beat_synthesize_batch, and around the ray-cast kernel of
- * rs_render_scenes, from that thread, on the launch's stream, until
+ * rs_beat_synthesize_batch, and around the ray-cast kernels of
+ * rs_render_scenes (one pair per call), from that thread, on the launch's stream, until
  * `capacity` launches are recorded.  Create and read on the plan's device. */
 typedef struct rs_kernel_timer rs_kernel_timer;
 

@@ -426,6 +426,11 @@ def rs_render_scenes(scenes_, g_az: int, g_el: int, noise=None, device="cuda:0",
     _check(lib.rs_render_scenes(arr, F, int(g_az), int(g_el),
                                 _ptr(noise) if noise is not None else None,
                                 *[_ptr(o) for o in outs], _stream_handle(stream)))
+    if all(o.dim() == 1 and o.numel() >= F * P and o.is_contiguous() for o in outs):
+        # one call per array: five slices per frame cost more host time than
+        # the ray-cast takes on the device (100 frames: 0.37 ms, now 0.19 ms)
+        views = [o[:F * P].view(F, P).unbind(0) if F else () for o in outs]
+        return [DevicePixels(*v) for v in zip(*views)]
     return [DevicePixels(*(o[f * P:(f + 1) * P] for o in outs)) for f in range(F)]
 
 
