@@ -44,7 +44,7 @@ TRAFFIC = {"sources": ("rs_mirror.hip", "rs_device.h", "rs_internal.h", "rs_spli
 # The same for one rs_range_doppler_ws call on the 100-frame walk (k_rd_fused,
 # k_rd_merge, k_rd_peak summed).
 RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_fft.h"),
-              "sources_sha256": "e69755b3be11e6fa24bfe29d4e6f0d7229154507f0cbfa6ba48f29b1a002b4ba",
+              "sources_sha256": "f2c047fa871e4e8fb97129bba6c78d11f724e03ec90261f78e98236317362f6b",
               "fetch_bytes": 2.0 * (158860 + 20534 + 52) * 1024, "write_bytes": (42880 + 12825 + 55) * 1024}
 
 

@@ -243,7 +243,8 @@ rs_status rs_plan_tune_cached(rs_plan *plan, const rs_pixels *pixels, void *cube
 rs_status rs_plan_describe(const rs_plan *plan, int64_t P, char *buf, size_t len);
 
 /* Enqueue the synthesis of one cube on `hip_stream`.  Split-K workspace is
- * taken from the device's stream-ordered pool and returned in stream order.
+ * kept with the plan for the stream (256 MiB at most), or taken from the
+ * device's stream-ordered pool and returned in stream order.
  * Errors: RS_E_INVALID (NULL plan/pixels/cube, P < 0 or > max_pixels, NULL
  * pixel pointer with P > 0), RS_E_NOMEM, RS_E_DEVICE. */
 rs_status rs_beat_synthesize(rs_plan *plan, const rs_pixels *pixels, void *cube,

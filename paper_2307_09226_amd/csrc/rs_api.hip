@@ -9,6 +9,7 @@
 #include <cstring>
 #include <cstdlib>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -169,38 +170,123 @@ rs_status rs_check_pixels(const rs_plan *pl, const rs_pixels *px)
 
 // ------------------------------------------------------------ workspaces --
 
-// Workspaces come from a pool of the plan, not the device's: the device's
-// pool hands its memory back at every synchronisation, and mapping 2 MiB or
-// more again costs a call 60-90 us (4,057-pixel request, waited for: 99 ->
-// 37 us; the 65,536-pixel NUFFT frame: 197 -> 119 us).  A plan's pool keeps at
-// most kPoolKeep bytes between calls and goes with the plan.  A stream under
-// capture takes the device's pool as before.
-constexpr uint64_t kPoolKeep = (uint64_t)256 << 20;
+// The allocating calls keep their workspaces with the plan: a block per
+// stream that uses it, found again by the next call on that stream.  Taking
+// one from the device's pool and handing it back cost a NUFFT request of
+// 5,204 pixels 20 us of host time a call (45 -> 25 us; a pool of its own for
+// each plan is worse: 76 us when three plans take turns), and a call that is
+// waited for 60-90 us more, as the device's pool
+// unmaps at every synchronisation (4,057-pixel request, waited for: 99 -> 37
+// us; the 65,536-pixel NUFFT frame 197 -> 119 us).
+// Blocks are powers of two, kBlocks of them and kKeepBytes in all at most,
+// and go with the plan.  A call owns its block from take to give, so calls
+// of several threads have a block each; the event recorded at give is waited
+// for at the next take, which costs nothing on the same stream and keeps a
+// stream that got the handle of a destroyed one behind its work.  Streams do
+// not take each other's blocks: that would order them.  Whatever finds no
+// block, and every call under capture, uses the device's pool.
+constexpr int kBlocks = 8;
+constexpr size_t kKeepBytes = (size_t)256 << 20;
+constexpr size_t kMinBlock = (size_t)64 << 10;
 
-static void pool_create(rs_plan *pl)
+struct rs_blocks {
+    struct block {
+        void *p = nullptr;
+        size_t bytes = 0;
+        hipStream_t st = nullptr;   // the stream of its last call
+        hipEvent_t used = nullptr;  // behind that call
+        bool taken = false;
+    };
+    std::mutex m;
+    block b[kBlocks];
+    int n = 0;
+    size_t total = 0;
+};
+
+static rs_blocks::block *block_take(rs_blocks *k, size_t bytes, hipStream_t st)
 {
-    hipMemPoolProps props;
-    std::memset(&props, 0, sizeof props);
-    props.allocType = hipMemAllocationTypePinned;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = pl->device;
-    if (hipMemPoolCreate(&pl->pool, &props) != hipSuccess) {
-        (void)hipGetLastError();
-        pl->pool = nullptr;
-        return;
+    size_t size = kMinBlock;
+    while (size < bytes && size <= kKeepBytes) size <<= 1;
+    rs_blocks::block *x = nullptr;
+    std::lock_guard<std::mutex> g(k->m);
+    for (int i = 0; i < k->n; ++i) {
+        rs_blocks::block &c = k->b[i];
+        if (!c.taken && c.st == st && c.bytes >= bytes && (!x || c.bytes < x->bytes)) x = &c;
     }
-    uint64_t keep = kPoolKeep;
-    (void)hipMemPoolSetAttribute(pl->pool, hipMemPoolAttrReleaseThreshold, &keep);
+    if (x) {
+        if (hipStreamWaitEvent(st, x->used, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        x->taken = true;
+        return x;
+    }
+    if (k->n == kBlocks || k->total + size > kKeepBytes) return nullptr;
+    x = &k->b[k->n];
+    if (!x->used && hipEventCreateWithFlags(&x->used, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        x->used = nullptr;
+        return nullptr;
+    }
+    if (hipMallocAsync(&x->p, size, st) != hipSuccess) {
+        (void)hipGetLastError();
+        x->p = nullptr;
+        return nullptr;
+    }
+    x->bytes = size;
+    x->st = st;
+    x->taken = true;
+    k->total += size;
+    ++k->n;
+    return x;
 }
 
-hipError_t rs_workspace_alloc(const rs_plan *pl, void **ws, size_t bytes, hipStream_t st)
+// The device is idle, or none of the plan's calls is in flight.
+static void blocks_destroy(rs_blocks *k)
 {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (pl->pool && hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-        if (hipMallocFromPoolAsync(ws, bytes, pl->pool, st) == hipSuccess) return hipSuccess;
-        (void)hipGetLastError();
+    for (int i = 0; i < kBlocks; ++i) {
+        if (k->b[i].p) (void)hipFree(k->b[i].p);
+        if (k->b[i].used) (void)hipEventDestroy(k->b[i].used);
     }
-    return hipMallocAsync(ws, bytes, st);
+    delete k;
+}
+
+rs_workspace::rs_workspace(const rs_plan *pl, size_t bytes, hipStream_t s) : st(s)
+{
+    if (!bytes) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (pl->blocks && hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        rs_blocks::block *x = block_take(pl->blocks, bytes, st);
+        if (x) {
+            owner = pl->blocks;
+            index = (int)(x - owner->b);
+            p = static_cast<char *>(x->p);
+            return;
+        }
+    }
+    void *v = nullptr;
+    if (hipMallocAsync(&v, bytes, st) == hipSuccess) p = static_cast<char *>(v);
+}
+
+rs_status rs_workspace::give(rs_status s)
+{
+    if (!p) return s;
+    hipError_t e;
+    const char *what;
+    if (owner) {
+        rs_blocks::block &x = owner->b[index];
+        what = "hipEventRecord";
+        e = hipEventRecord(x.used, st);
+        if (e != hipSuccess) (void)hipStreamSynchronize(st);
+        std::lock_guard<std::mutex> g(owner->m);
+        x.taken = false;
+    } else {
+        what = "hipFreeAsync";
+        e = hipFreeAsync(p, st);
+    }
+    p = nullptr;
+    if (e != hipSuccess && s == RS_OK) s = rs_fail(RS_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
+    return s;
 }
 
 // ---------------------------------------------------------- kernel timer --
@@ -437,7 +523,7 @@ static rs_status plan_common(const rs_radar *r, rs_form form, rs_dtype dtype, in
             return rs_fail(RS_E_DEVICE, "copy of the NUFFT deconvolution table failed");
         }
     }
-    pool_create(pl);
+    pl->blocks = new (std::nothrow) rs_blocks;
     *out = pl;
     return RS_OK;
 }
@@ -515,7 +601,7 @@ extern "C" void rs_plan_destroy(rs_plan *pl)
         device_guard g(pl->device);
         if (pl->d_ant) (void)hipFree(pl->d_ant);  // waits for the device: no workspace is in use after it
         if (pl->d_deconv) (void)hipFree(pl->d_deconv);
-        if (pl->pool) (void)hipMemPoolDestroy(pl->pool);
+        if (pl->blocks) blocks_destroy(pl->blocks);
     }
     delete pl;
 }
@@ -776,15 +862,10 @@ extern "C" rs_status rs_beat_synthesize(rs_plan *pl, const rs_pixels *px, void *
     device_guard g(pl->device);
     if (g.st != RS_OK) return g.st;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    void *ws = nullptr;
-    if (need > 0 && rs_workspace_alloc(pl, &ws, need, st) != hipSuccess)
+    rs_workspace ws(pl, need, st);
+    if (need > 0 && !ws.p)
         return rs_fail(RS_E_NOMEM, "stream-ordered workspace allocation of %zu bytes failed", need);
-    s = rs_beat_synthesize_ws(pl, px, cube, ws, need, stream);
-    if (ws) {
-        hipError_t e = hipFreeAsync(ws, st);
-        if (e != hipSuccess && s == RS_OK) s = rs_fail(RS_E_DEVICE, "hipFreeAsync: %s", hipGetErrorString(e));
-    }
-    return s;
+    return ws.give(rs_beat_synthesize_ws(pl, px, cube, ws.p, need, stream));
 }
 
 // ------------------------------------------------ allocation-free call ----
@@ -865,17 +946,13 @@ extern "C" rs_status rs_beat_synthesize_batch(rs_plan *pl, const rs_pixels *fram
         int64_t pmax = 0;
         for (int f = 0; f < nframes; ++f) pmax = frames[f].P > pmax ? frames[f].P : pmax;
         const size_t need = rs_nufft_workspace(pl, pmax);
-        void *ws = nullptr;
-        if (need > 0 && rs_workspace_alloc(pl, &ws, need, st) != hipSuccess)
+        rs_workspace ws(pl, need, st);
+        if (need > 0 && !ws.p)
             return rs_fail(RS_E_NOMEM, "stream-ordered workspace allocation of %zu bytes failed", need);
         s = RS_OK;
         for (int f = 0; f < nframes && s == RS_OK; ++f)
-            s = rs_nufft_enqueue(pl, &frames[f], static_cast<char *>(cubes) + f * cube_bytes_f, ws, st);
-        if (ws) {
-            const hipError_t e = hipFreeAsync(ws, st);
-            if (e != hipSuccess && s == RS_OK) s = rs_fail(RS_E_DEVICE, "hipFreeAsync: %s", hipGetErrorString(e));
-        }
-        return s;
+            s = rs_nufft_enqueue(pl, &frames[f], static_cast<char *>(cubes) + f * cube_bytes_f, ws.p, st);
+        return ws.give(s);
     }
 
     const size_t cube_bytes = (size_t)pl->C * pl->L * pl->Ns * (pl->dtype == RS_C128 ? 16 : 8);
@@ -898,8 +975,9 @@ extern "C" rs_status rs_beat_synthesize_batch(rs_plan *pl, const rs_pixels *fram
         chunks += S;
         off += rs_workspace_bytes(pl, S);
     }
-    char *ws = nullptr;
-    if (rs_workspace_alloc(pl, reinterpret_cast<void **>(&ws), off, st) != hipSuccess)
+    rs_workspace kept(pl, off, st);
+    char *const ws = kept.p;
+    if (!ws)
         return rs_fail(RS_E_NOMEM, "stream-ordered workspace allocation of %zu bytes failed", off);
     for (int f = 0; f < nframes; ++f) {
         rs_job j = rs_make_job(pl, &frames[f], jobs[f].cube, ws + offs[f], jobs[f].S, jobs[f].chunk);
@@ -913,7 +991,7 @@ extern "C" rs_status rs_beat_synthesize_batch(rs_plan *pl, const rs_pixels *fram
     hipError_t e = hipMemcpyAsync(djobs, jobs.data(), jobs.size() * sizeof(rs_job),
                                   hipMemcpyHostToDevice, st);
     if (e != hipSuccess) {
-        (void)hipFreeAsync(ws, st);
+        (void)kept.give(RS_E_DEVICE);
         return rs_fail(RS_E_DEVICE, "job table copy: %s", hipGetErrorString(e));
     }
     rs_launch L;
@@ -941,7 +1019,5 @@ extern "C" rs_status rs_beat_synthesize_batch(rs_plan *pl, const rs_pixels *fram
         R.total = outs;
         s = rs_launch_reduce_checked(pl, R, st);
     }
-    e = hipFreeAsync(ws, st);
-    if (e != hipSuccess && s == RS_OK) s = rs_fail(RS_E_DEVICE, "hipFreeAsync: %s", hipGetErrorString(e));
-    return s;
+    return kept.give(s);
 }

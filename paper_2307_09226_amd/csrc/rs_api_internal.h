@@ -13,7 +13,7 @@ struct rs_plan {
     double Ka = 0;                  // 2 fc / c0, the far-field angle term (not switched by carrier)
     int32_t model = 0;              // rs_model_flags
     double *d_ant = nullptr;        // device tx[M][3] then rx[N][3]
-    hipMemPool_t pool = nullptr;    // workspaces of the allocating calls (rs_workspace_alloc)
+    struct rs_blocks *blocks = nullptr;  // workspaces of the allocating calls (rs_workspace)
     rs_form form = RS_FORM_MFMA_SPLIT16;
     rs_dtype dtype = RS_C64;
     int64_t max_pixels = 0;
@@ -53,8 +53,18 @@ struct device_guard {
     }
 };
 void rs_choose_tiles(rs_plan *pl);
-// Stream-ordered workspace of one call, released with hipFreeAsync.
-hipError_t rs_workspace_alloc(const rs_plan *pl, void **ws, size_t bytes, hipStream_t st);
+// Stream-ordered workspace of one call on st: p is NULL where there is none.
+// give returns it behind the call's work and passes the call's status on.
+struct rs_workspace {
+    char *p = nullptr;
+    rs_workspace(const rs_plan *pl, size_t bytes, hipStream_t st);
+    rs_status give(rs_status s);
+
+private:
+    hipStream_t st;
+    rs_blocks *owner = nullptr;  // the plan's blocks, or NULL for the device's pool
+    int index = 0;
+};
 rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *chunk);
 size_t rs_partial_bytes(const rs_plan *pl, int32_t S);
 size_t rs_workspace_bytes(const rs_plan *pl, int32_t S);   // partials (+ chunk scales with strengths per block)

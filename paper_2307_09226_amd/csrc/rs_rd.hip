@@ -1062,13 +1062,10 @@ extern "C" rs_status rs_range_doppler(rs_plan *pl, const void *cubes, int32_t nf
     if (g.st != RS_OK) return g.st;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const rd_layout y = rd_plan_layout(pl, nframes, power != nullptr);
-    char *ws = nullptr;
-    if (rs_workspace_alloc(pl, reinterpret_cast<void **>(&ws), y.total, st) != hipSuccess)
+    rs_workspace ws(pl, y.total, st);
+    if (!ws.p)
         return rs_fail(RS_E_NOMEM, "stream-ordered workspace allocation of %zu bytes failed", y.total);
-    rs_status s = rd_run(pl, y, cubes, nframes, skip_static, power, doppler_time, peaks, ws, logn, logl, st);
-    const hipError_t e = hipFreeAsync(ws, st);
-    if (e != hipSuccess && s == RS_OK) s = rs_fail(RS_E_DEVICE, "hipFreeAsync: %s", hipGetErrorString(e));
-    return s;
+    return ws.give(rd_run(pl, y, cubes, nframes, skip_static, power, doppler_time, peaks, ws.p, logn, logl, st));
 }
 
 extern "C" rs_status rs_range_doppler_ws(rs_plan *pl, const void *cubes, int32_t nframes, int32_t skip_static,
