@@ -100,14 +100,31 @@ __device__ __forceinline__ float2 rs_gload2(const float2 *p, int64_t i)
     return make_float2(__uint_as_float((unsigned)(v & 0xffffffffu)), __uint_as_float((unsigned)(v >> 32)));
 }
 
+// Correctly rounded square root of q in [2^-24, 1], the values 1 - z z takes:
+// the hardware's root s and Tuckerman's test s (s - ulp) < q <= s (s + ulp),
+// without the general function's scaling of small arguments.
+__device__ __forceinline__ float sqrt_unit(float q)
+{
+    const float s = __builtin_amdgcn_sqrtf(q);
+    const float dn = __int_as_float(__float_as_int(s) - 1), up = __int_as_float(__float_as_int(s) + 1);
+    const float r = __builtin_fmaf(-dn, s, q) <= 0.0f ? dn : s;
+    return __builtin_fmaf(-up, s, q) > 0.0f ? up : r;
+}
+
 // Kernel weight at offset t (cells) from the point; zero outside |t| <= w/2.
 template <int W>
 __device__ __forceinline__ float es_weight(float t, float beta)
 {
     const float z = t * (2.0f / W);
     const float q = 1.0f - z * z;
-    return q > 0.0f ? expf(beta * (__builtin_sqrtf(q) - 1.0f)) : 0.0f;
+    const float w = expf(beta * (sqrt_unit(q) - 1.0f));
+    return q > 0.0f ? w : 0.0f;
 }
+
+// a / b for 0 <= a < 2^20 and rb = recip(b): (a + 1/2) / b is 1/(2 b) away
+// from every whole number, and the error of the product stays below that.
+__device__ __forceinline__ float recip(int b) { return __builtin_amdgcn_rcpf((float)b); }
+__device__ __forceinline__ int small_div(int a, float rb) { return (int)(((float)a + 0.5f) * rb); }
 
 __global__ __launch_bounds__(256) void k_nufft_zero(float4 *p, int64_t n4)
 {
@@ -131,19 +148,44 @@ __device__ __forceinline__ int block_reduce(int v, int *red, bool is_min)
     return r;
 }
 
+// v of another lane by a row operation of the vector unit, `old` where there
+// is none: rows of 16 lanes shifted up by n (0x110 + n), lane 15 of a row to
+// the next row (0x142), lane 31 to the upper half (0x143).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ int lane_op(int old, int v)
+{
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+
+// Minimum over the wave, in lane 63.
+__device__ __forceinline__ int wave_min(int v)
+{
+    v = min(v, lane_op<0x111>(INT_MAX, v));
+    v = min(v, lane_op<0x112>(INT_MAX, v));
+    v = min(v, lane_op<0x114>(INT_MAX, v));
+    v = min(v, lane_op<0x118>(INT_MAX, v));
+    v = min(v, lane_op<0x142>(INT_MAX, v));
+    return min(v, lane_op<0x143>(INT_MAX, v));
+}
+
+// Sum over the lanes up to the own one.
+__device__ __forceinline__ int wave_sum_to(int v)
+{
+    v += lane_op<0x111>(0, v);
+    v += lane_op<0x112>(0, v);
+    v += lane_op<0x114>(0, v);
+    v += lane_op<0x118>(0, v);
+    v += lane_op<0x142, 0xa>(0, v);   // rows 1 and 3 take the row before
+    return v + lane_op<0x143, 0xc>(0, v);   // rows 2 and 3 the lower half
+}
+
 // Block-wide component-wise minimum of v; every thread gets it (a maximum
 // is taken as the minimum of ~x, which is order-reversing and cannot
 // overflow).
 __device__ __forceinline__ int4 block_min4(int4 v, int4 *red)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        v.x = min(v.x, __shfl_xor(v.x, o));
-        v.y = min(v.y, __shfl_xor(v.y, o));
-        v.z = min(v.z, __shfl_xor(v.z, o));
-        v.w = min(v.w, __shfl_xor(v.w, o));
-    }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    const int4 m = make_int4(wave_min(v.x), wave_min(v.y), wave_min(v.z), wave_min(v.w));
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = m;
     __syncthreads();
     int4 r = red[0];
     for (int i = 1; i < kSpreadThreads / 64; ++i) {
@@ -159,9 +201,10 @@ __device__ __forceinline__ int4 block_min4(int4 v, int4 *red)
 //      (m1, m2) of its W x W window, its strength c and the 2 W kernel
 //      weights; the block's bounding box of cells follows by reduction (and
 //      a tall box of two row groups is split into two sub-boxes).
-//   2. The points are sorted by (sub-box, window column, index) -- a rank
-//      sort of unique keys, so the order is fixed -- and cs[k] marks where
-//      column k starts.
+//   2. The points are sorted by (sub-box, window column, index): a bit per
+//      point in its column's mask; the masks' counts, summed over the
+//      columns, give cs[k], where column k starts, and the bits below a
+//      point's own its place in the column.
 //   3. A thread per box column (and share of its candidates) sums, in
 //      registers, c w1[x - m1] w2[y - m2] over the points whose window
 //      covers it -- those with m1 - lo1 in [x - W + 1, x], a contiguous run
@@ -171,24 +214,25 @@ __device__ __forceinline__ int4 block_min4(int4 v, int4 *red)
 // No LDS atomics: neighbouring pixels share most of their window, and
 // atomics on the same LDS cells from successive instructions serialise.
 // Under 40 KB of LDS for W <= 7 and under 128 VGPRs: four workgroups per CU.
+// Bound by the vector instructions it issues (71 % of the issue slots over a
+// frame of 65,536 pixels and 12 channels, W = 7).
 template <int W>
 __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
 {
-    __shared__ int pm1[kBlockPts], pm2[kBlockPts];
     __shared__ float pw1[kBlockPts * W], pw2[kBlockPts * W];
     __shared__ int cs[kMaxCols + 1];
     __shared__ int2 srec[kBlockPts];      // sorted: ((m1 - lo1) | (m2 - lo2) << 16, point index)
     __shared__ float2 spc[kBlockPts];     // sorted strengths
     // per-share accumulators [share][row][column]; before them, in the same
-    // space, each sorted point's w2 placed at its row of the box (16 rows).
-    // Until the sorted records are complete the space holds the points'
-    // strengths, the sort keys and the start-row occupancy of the split.
+    // space, the columns' point masks (a word per 32 points and column), then
+    // each sorted point's w2 placed at its row of the box (16 rows)
     __shared__ __align__(16) float accbuf[2 * kAccCells];   // read as float4
     float *accr = accbuf, *acci = accbuf + kAccCells, *spw2r = accbuf;
-    float2 *pc = reinterpret_cast<float2 *>(accbuf);                          // [kBlockPts]
-    int *key = reinterpret_cast<int *>(accbuf + 2 * kBlockPts);               // [kBlockPts], read as int4
-    unsigned *occ = reinterpret_cast<unsigned *>(accbuf + 3 * kBlockPts);     // [kGapRows / 32]
-    static_assert(3 * kBlockPts + kGapRows / 32 <= 2 * kAccCells, "aliases fit the accumulator space");
+    unsigned *mask = reinterpret_cast<unsigned *>(accbuf);                    // [kBlockPts / 32][kMaxCols]
+    unsigned *occ = reinterpret_cast<unsigned *>(cs);                         // [kGapRows / 32], the split's
+    static_assert(kBlockPts / 32 * kMaxCols <= 2 * kAccCells, "the masks fit the accumulator space");
+    static_assert(kGapRows / 32 <= kMaxCols, "the start-row occupancy fits the column table");
+    static_assert(kSpreadThreads == kBlockPts && kMaxCols == 2 * kSpreadThreads, "a point, two columns per thread");
     __shared__ int red[kSpreadThreads / 64];
     __shared__ int4 red4[kSpreadThreads / 64];
     const int tid = threadIdx.x;
@@ -202,9 +246,15 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
     }
     const int64_t p0 = (int64_t)blockIdx.x * kBlockPts;
     const int npts = (int)min<int64_t>(kBlockPts, A.P - p0);
+    const bool have = tid < npts;
+    for (int i = tid; i < 2 * kAccCells / 4; i += kSpreadThreads)
+        reinterpret_cast<uint4 *>(mask)[i] = make_uint4(0u, 0u, 0u, 0u);
     int lo1 = INT_MAX, hi1 = INT_MIN, lo2 = INT_MAX, hi2 = INT_MIN;
-    for (int q = tid; q < npts; q += kSpreadThreads) {
-        const int64_t p = p0 + q;
+    int c1 = 0, c2 = 0;                   // first cell of the thread's point's window
+    float2 cq = make_float2(0.f, 0.f);    // its strength
+    float w2q[W];                         // its weights along l
+    if (have) {
+        const int64_t p = p0 + tid;
         double psi, b, beta;
         rs_chan_args(A, rs_gload(A.x, p), rs_gload(A.y, p), rs_gload(A.z, p), rs_gload(A.vr, p), m, tx, rx, &psi,
                      &b, &beta);
@@ -215,25 +265,23 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         float sn, cs_;
         sincospif(2.0f * (float)th, &sn, &cs_);
         const float a = rs_gload(A.amp, p);
-        pc[q] = make_float2(a * cs_, a * sn);
+        cq = make_float2(a * cs_, a * sn);
         // first cell of the W-cell window and the weights at its cells; the
         // offset from the point is formed in binary64 so that the weights see
         // it to float32 precision whatever the grid size
         const double t1 = u * (double)A.n1, t2 = v * (double)A.n2;
         const double s1 = __builtin_ceil(t1 - 0.5 * W), s2 = __builtin_ceil(t2 - 0.5 * W);
-        const int c1 = (int)s1, c2 = (int)s2;
-        pm1[q] = c1;
-        pm2[q] = c2;
+        c1 = (int)s1;
+        c2 = (int)s2;
         const float o1 = (float)(s1 - t1), o2 = (float)(s2 - t2);
 #pragma unroll
         for (int i = 0; i < W; ++i) {
-            pw1[q * W + i] = es_weight<W>(o1 + (float)i, A.beta);
-            pw2[q * W + i] = es_weight<W>(o2 + (float)i, A.beta);
+            pw1[tid * W + i] = es_weight<W>(o1 + (float)i, A.beta);
+            w2q[i] = es_weight<W>(o2 + (float)i, A.beta);
+            pw2[tid * W + i] = w2q[i];
         }
-        lo1 = min(lo1, c1);
-        hi1 = max(hi1, c1);
-        lo2 = min(lo2, c2);
-        hi2 = max(hi2, c2);
+        lo1 = hi1 = c1;
+        lo2 = hi2 = c2;
     }
     int4 *dsc = A.desc + ((int64_t)c * A.nblk + blockIdx.x) * 2;
     {   // the barriers also publish the points
@@ -259,10 +307,7 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
     if (e2 > kRowsReg && hi2 - lo2 < kGapRows) {   // uniform
         for (int w = tid; w < kGapRows / 32; w += kSpreadThreads) occ[w] = 0u;
         __syncthreads();
-        for (int q = tid; q < npts; q += kSpreadThreads) {
-            const int rr = pm2[q] - lo2;
-            atomicOr(&occ[rr >> 5], 1u << (rr & 31));
-        }
+        if (have) atomicOr(&occ[(c2 - lo2) >> 5], 1u << ((c2 - lo2) & 31));
         __syncthreads();
         // every run of occupied rows that ends at r < span - 1 is followed by
         // a gap up to the next occupied row (row span - 1 is occupied); key:
@@ -285,14 +330,11 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
             const int e2a = rsp + W, e2b = (span - 1) - (rsp + gap) + W;
             if (e2a <= kRowsReg && e2b <= kRowsReg && e2a <= A.n2 && e2b <= A.n2) {   // uniform
                 int alo = INT_MAX, ahi = INT_MIN, blo = INT_MAX, bhi = INT_MIN;
-                for (int q = tid; q < npts; q += kSpreadThreads) {
-                    if (pm2[q] - lo2 <= rsp) {
-                        alo = min(alo, pm1[q]);
-                        ahi = max(ahi, pm1[q]);
-                    } else {
-                        blo = min(blo, pm1[q]);
-                        bhi = max(bhi, pm1[q]);
-                    }
+                if (have) {
+                    if (c2 - lo2 <= rsp)
+                        alo = ahi = c1;
+                    else
+                        blo = bhi = c1;
                 }
                 const int4 ab = block_min4(make_int4(alo, ~ahi, blo, ~bhi), red4);
                 alo = ab.x;
@@ -330,13 +372,19 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
     if (nsb == 1 && (hi1 - lo1 >= kMaxCols || e1 > A.n1 || e2 > A.n2)) {
         // box wider than the grid or the column table: scatter each weight
         // to the grid (a lane per window cell, a wave per point)
+        if (have) {
+            srec[tid] = make_int2(c1, c2);
+            spc[tid] = cq;
+        }
+        __syncthreads();
         const int lane = tid & 63, wave = tid >> 6;
         const int i = lane % W, j = lane / W;
         if (lane < W * W) {
             for (int q = wave; q < npts; q += kSpreadThreads / 64) {
                 const float w = pw1[q * W + i] * pw2[q * W + j];
-                const float2 cv = pc[q];
-                float2 *cell = grid + (int64_t)pmod(pm2[q] + j, A.n2) * A.n1 + pmod(pm1[q] + i, A.n1);
+                const float2 cv = spc[q];
+                const int2 at = srec[q];
+                float2 *cell = grid + (int64_t)pmod(at.y + j, A.n2) * A.n1 + pmod(at.x + i, A.n1);
                 gatomic_add(&cell->x, cv.x * w);
                 gatomic_add(&cell->y, cv.y * w);
             }
@@ -344,72 +392,67 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         return;
     }
 
-    // ---- 2. sort by sub-box and window column: key = column * kBlockPts + q,
-    // the columns of the second sub-box numbered after those of the first;
-    // a rank sort (no barriers inside) ----------------------------------------
+    // ---- 2. sort by sub-box, window column and index, the columns of the
+    // second sub-box numbered after those of the first.  The masks were
+    // cleared at the start, before the barriers of the bounding box. --------
     const int ncolA = be1[0] - W + 1;
     const int ncol = ncolA + (nsb == 2 ? be1[1] - W + 1 : 0);
-    auto group = [&](int q) { return nsb == 2 && pm2[q] - lo2 > split ? 1 : 0; };
-    for (int q = tid; q < kBlockPts; q += kSpreadThreads) {
-        if (q < npts) {
-            const int g = group(q);
-            key[q] = ((g ? ncolA : 0) + pm1[q] - blo1[g]) * kBlockPts + q;
-        } else {
-            key[q] = INT_MAX;
-        }
-    }
+    const bool second = nsb == 2 && c2 - lo2 > split;
+    const int col1 = c1 - (second ? blo1[1] : blo1[0]);
+    const int col = (second ? ncolA : 0) + col1;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (have) atomicOr(&mask[(tid >> 5) * kMaxCols + col], 1u << (tid & 31));
     __syncthreads();
-    // the sorted position of a point is the number of smaller keys (the keys
-    // are unique, so the ranks are a permutation); every lane of a wave
-    // reads the same keys at once, which the LDS broadcasts.  The records
-    // (offsets from their sub-box's corner) are stored in sorted order so
-    // that the gather reads them without an indirection.
-    // Each point also lays out its w2 at its row of the (sub-)box, 16 rows
-    // from its sorted position (what the register gather reads), into the
-    // space that held the keys and strengths: both are read first.
-    static_assert(kSpreadThreads == kBlockPts, "one point per thread");
-    int rank = 0;
-    float2 cq = make_float2(0.f, 0.f);
-    if (tid < npts) {
-        const int k = key[tid];
-        const int4 *k4 = reinterpret_cast<const int4 *>(key);
-#pragma unroll 4
-        for (int i = 0; i < kBlockPts / 4; ++i) {
-            const int4 v = k4[i];
-            rank += (v.x < k) + (v.y < k) + (v.z < k) + (v.w < k);
-        }
-        cq = pc[tid];
+    int rank = 0;   // points of the same column with a smaller index
+    if (have) {
+        for (int w = 0; w < wave; ++w)
+            rank += __builtin_popcount(mask[2 * w * kMaxCols + col]) +
+                    __builtin_popcount(mask[(2 * w + 1) * kMaxCols + col]);
+        rank = __builtin_amdgcn_mbcnt_lo(mask[2 * wave * kMaxCols + col], rank);
+        rank = __builtin_amdgcn_mbcnt_hi(mask[(2 * wave + 1) * kMaxCols + col], rank);
     }
-    __syncthreads();   // every key and strength has been read
-    if (tid < npts) {
-        const int g = group(tid);
-        const int row = pm2[tid] - blo2[g];
-        srec[rank] = make_int2((pm1[tid] - blo1[g]) | (row << 16), tid);
+    // columns 2 tid, 2 tid + 1: their counts, summed over the wave
+    int n0 = 0, n1 = 0, incl = 0;
+    if (128 * wave < ncol) {   // uniform in the wave; columns from ncol on are empty
+#pragma unroll
+        for (int w = 0; w < kBlockPts / 32; ++w) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(mask + w * kMaxCols + 2 * tid);
+            n0 += __builtin_popcount(v.x);
+            n1 += __builtin_popcount(v.y);
+        }
+        incl = wave_sum_to(n0 + n1);
+    }
+    if (lane == 63) red[wave] = incl;
+    __syncthreads();   // ... and every mask has been read
+    int before = incl - n0 - n1;
+#pragma unroll
+    for (int w = 0; w < kSpreadThreads / 64; ++w) before += w < wave ? red[w] : 0;
+    // cs[k] = first sorted position whose column is >= k, k = 0 .. ncol
+    cs[2 * tid] = before;
+    cs[2 * tid + 1] = before + n0;
+    if (tid == 0) cs[kMaxCols] = npts;
+    __syncthreads();
+    // The records (offsets from their sub-box's corner) are stored in sorted
+    // order so that the gather reads them without an indirection, and each
+    // point lays out its w2 at its row of the (sub-)box, 16 rows from its
+    // sorted position (what the register gather reads).
+    if (have) {
+        rank += cs[col];
+        const int row = c2 - (second ? blo2[1] : blo2[0]);
+        srec[rank] = make_int2(col1 | (row << 16), tid);
         spc[rank] = cq;
+        float w[kRowsReg];
+#pragma unroll
+        for (int r = 0; r < kRowsReg; ++r) w[r] = r < W ? w2q[r < W ? r : 0] : 0.f;
+        // moved up by the row, a bit at a time (rows past 15 have no register gather)
+#pragma unroll
+        for (int k = 1; k < kRowsReg; k <<= 1)
+#pragma unroll
+            for (int r = kRowsReg - 1; r >= 0; --r) w[r] = row & k ? (r >= k ? w[r >= k ? r - k : 0] : 0.f) : w[r];
         float4 *dst = reinterpret_cast<float4 *>(spw2r + rank * kRowsReg);
 #pragma unroll
-        for (int r4 = 0; r4 < kRowsReg / 4; ++r4) {
-            float w[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int d = 4 * r4 + j - row;
-                w[j] = d >= 0 && d < W ? pw2[tid * W + d] : 0.f;
-            }
-            dst[r4] = make_float4(w[0], w[1], w[2], w[3]);
-        }
-    }
-    __syncthreads();
-    // cs[k] = first sorted position whose column is >= k, k = 0 .. ncol
-    auto column = [&](int s) {
-        const int2 rec = srec[s];
-        return (group(rec.y) ? ncolA : 0) + (rec.x & 0xffff);
-    };
-    for (int s = tid; s < npts; s += kSpreadThreads) {
-        const int col = column(s);
-        const int prev = s == 0 ? -1 : column(s - 1);
-        for (int k = prev + 1; k <= col; ++k) cs[k] = s;
-        if (s == npts - 1)
-            for (int k = col + 1; k <= ncol; ++k) cs[k] = npts;
+        for (int r4 = 0; r4 < kRowsReg / 4; ++r4)
+            dst[r4] = make_float4(w[4 * r4], w[4 * r4 + 1], w[4 * r4 + 2], w[4 * r4 + 3]);
     }
     __syncthreads();
 
@@ -418,7 +461,7 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
     // of its private LDS accumulator; the shares are then added in a fixed
     // order per cell ---------------------------------------------------------
     const int E = e1 * e2;
-    const int nparts = slot ? min(kSpreadThreads / e1, kAccCells / E) : 0;
+    const int nparts = slot ? min(small_div(kSpreadThreads, recip(e1)), small_div(kAccCells, recip(E))) : 0;
     // (Sub-)boxes of at most 16 rows: the row sums of a column live in
     // registers, and each point's w2 is laid out at its row offset (by the
     // sort) so that a candidate costs four LDS vector reads and 32 FMAs.  TWO
@@ -431,13 +474,16 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         // worth each), its shares leave room for one of the second
         const int EA = be1[0] * be2[0], EB = TWO ? be1[1] * be2[1] : 0;
         const int nA = TWO ? cs[ncolA] : npts;   // points of the first sub-box
-        const int tA = TWO ? min(max(kSpreadThreads * nA / npts, be1[0]), kSpreadThreads - be1[1]) : kSpreadThreads;
-        const int pA = min(tA / be1[0], (kAccCells - EB) / EA);
-        const int pB = TWO ? min((kSpreadThreads - tA) / be1[1], (kAccCells - pA * EA) / EB) : 0;
+        const int tA = TWO ? min(max(small_div(kSpreadThreads * nA, recip(npts)), be1[0]), kSpreadThreads - be1[1])
+                           : kSpreadThreads;
+        const int pA = min(small_div(tA, recip(be1[0])), small_div(kAccCells - EB, recip(EA)));
+        const int pB = TWO ? min(small_div(kSpreadThreads - tA, recip(be1[1])),
+                                 small_div(kAccCells - pA * EA, recip(EB)))
+                           : 0;
         const int g = TWO && tid >= tA ? 1 : 0;
         const int tl = g ? tid - tA : tid;
         const int ex = g ? be1[1] : be1[0], ey = g ? be2[1] : be2[0];
-        const int x = tl % ex, p = tl / ex;
+        const int p = small_div(tl, recip(ex)), x = tl - p * ex;
         const int np = g ? pB : pA;
         const int coff = g ? ncolA : 0, ncg = g ? ncol - ncolA : ncolA;
         float ar[kRowsReg], ai[kRowsReg];
@@ -446,7 +492,8 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         if (p < np) {
             const int k0 = max(0, x - W + 1), k1 = min(x, ncg - 1);
             const int sb = cs[coff + k0], len = cs[coff + k1 + 1] - sb;
-            const int s_beg = sb + len * p / np, s_end = sb + len * (p + 1) / np;
+            const float rnp = recip(np);
+            const int s_beg = sb + small_div(len * p, rnp), s_end = sb + small_div(len * (p + 1), rnp);
             for (int s = s_beg; s < s_end; ++s) {
                 const int2 rec = srec[s];
                 const float2 cv = spc[s];
