@@ -61,11 +61,15 @@ rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *ch
     if (ch < pl->min_chunk) ch = pl->min_chunk;
     // Few pixels: where the smallest chunk leaves compute units without a
     // work item, finer chunks (whole steps), as long as the partial sums stay
-    // within 16 MiB.  1 x 4, Ns 128, L 64, 4,057 pixels: 38 us with 4 chunks of
-    // 1,024, 20.5 us with 16 of 256, 20.6 us with 32 of 128, 25.4 us with 64
-    // of 64 (the reduction grows); plain form, 2 x 4, 64 x 32, 4,096 pixels: 31.6 us with chunks of
-    // 256, 28.7 us with 128 (256 work items).
-    const int64_t fine = pl->mirror ? 256 : (pl->form == RS_FORM_FP64_DIRECT ? 64 : 0);
+    // within 16 MiB.  A batch forms its frames' sums in the same chunks (its
+    // cubes have the bits of single calls), and there the partial sums only
+    // cost traffic, hence no finer than this.  1 x 4, Ns 128, L 64, 4,057
+    // pixels: 40 us with 4 chunks of 1,024, 29 us with 7 of 640, 23 us with 16
+    // of 256; 200 such frames in a batch: 458, 523 and 795 us.  3 x 4, 256 x
+    // 64, 47 frames of 4,641 pixels: 453, 508, and 654 us with chunks of 512.
+    // Plain form, 2 x 4, 64 x 32, 4,096 pixels: 31.6 us with chunks of 256, 28.7
+    // us with 128 (256 work items).
+    const int64_t fine = pl->mirror ? 640 : (pl->form == RS_FORM_FP64_DIRECT ? 128 : 0);
     const int64_t items = (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
     if (fine > 0 && (P + ch - 1) / ch * items < pl->ncu) {
         const int64_t cube = (int64_t)pl->C * pl->L * pl->Ns * (pl->mirror ? 8 : 16);
