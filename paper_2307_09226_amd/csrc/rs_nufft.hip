@@ -56,6 +56,7 @@ constexpr int kMaxCols = 512;                         // widest box gathered per
 constexpr int kSlot = 1024;                           // tile cells kept per (block, channel)
 constexpr int kAccCells = 2048;                       // LDS accumulator cells of the column gather
 constexpr int kRowsReg = 16;                          // box rows held in registers by the column gather
+constexpr int kRowsLow = 8;                           // ... where every (sub-)box is as low as this
 constexpr int kGapRows = 1024;                        // tallest box searched for a row gap to split at
 constexpr int kMaskBlocks = 1024;                     // descriptor entries per coverage pass of a row
 constexpr int kAsmGroups = 8192;                      // assembly workgroups enough for 256 columns each
@@ -434,8 +435,11 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
     __syncthreads();
     // The records (offsets from their sub-box's corner) are stored in sorted
     // order so that the gather reads them without an indirection, and each
-    // point lays out its w2 at its row of the (sub-)box, 16 rows from its
-    // sorted position (what the register gather reads).
+    // point lays out its w2 at its row of the (sub-)box, kRowsReg rows from
+    // its sorted position (what the register gather reads); low boxes, those
+    // of points that share a Doppler window, kRowsLow rows and a pad of four
+    // that spreads the points over the LDS banks.
+    const bool low = W <= kRowsLow && be2[0] <= kRowsLow && be2[1] <= kRowsLow;
     if (have) {
         rank += cs[col];
         const int row = c2 - (second ? blo2[1] : blo2[0]);
@@ -449,10 +453,11 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         for (int k = 1; k < kRowsReg; k <<= 1)
 #pragma unroll
             for (int r = kRowsReg - 1; r >= 0; --r) w[r] = row & k ? (r >= k ? w[r >= k ? r - k : 0] : 0.f) : w[r];
-        float4 *dst = reinterpret_cast<float4 *>(spw2r + rank * kRowsReg);
+        float4 *dst = reinterpret_cast<float4 *>(spw2r + rank * (low ? kRowsLow + 4 : kRowsReg));
 #pragma unroll
         for (int r4 = 0; r4 < kRowsReg / 4; ++r4)
-            dst[r4] = make_float4(w[4 * r4], w[4 * r4 + 1], w[4 * r4 + 2], w[4 * r4 + 3]);
+            if (r4 < kRowsLow / 4 || !low)
+                dst[r4] = make_float4(w[4 * r4], w[4 * r4 + 1], w[4 * r4 + 2], w[4 * r4 + 3]);
     }
     __syncthreads();
 
@@ -464,11 +469,12 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
     const int nparts = slot ? min(small_div(kSpreadThreads, recip(e1)), small_div(kAccCells, recip(E))) : 0;
     // (Sub-)boxes of at most 16 rows: the row sums of a column live in
     // registers, and each point's w2 is laid out at its row offset (by the
-    // sort) so that a candidate costs four LDS vector reads and 32 FMAs.  TWO
-    // (two sub-boxes) is a compile-time flag, so that the one-box case keeps
-    // its simple indexing.
-    auto register_gather = [&](auto two_t) {
+    // sort) so that a candidate costs four LDS vector reads and 32 FMAs, half
+    // of them in low boxes.  TWO (two sub-boxes) is a compile-time flag, so
+    // that the one-box case keeps its simple indexing.
+    auto register_gather = [&](auto two_t, auto rows_t) {
         constexpr bool TWO = decltype(two_t)::value;
+        constexpr int RR = decltype(rows_t)::value, RS = RR == kRowsReg ? kRowsReg : RR + 4;
         // threads, shares and accumulator cells of the sub-boxes: the first
         // takes threads in proportion to its points (at least a column's
         // worth each), its shares leave room for one of the second
@@ -486,9 +492,9 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         const int p = small_div(tl, recip(ex)), x = tl - p * ex;
         const int np = g ? pB : pA;
         const int coff = g ? ncolA : 0, ncg = g ? ncol - ncolA : ncolA;
-        float ar[kRowsReg], ai[kRowsReg];
+        float ar[RR], ai[RR];
 #pragma unroll
-        for (int r = 0; r < kRowsReg; ++r) ar[r] = ai[r] = 0.f;
+        for (int r = 0; r < RR; ++r) ar[r] = ai[r] = 0.f;
         if (p < np) {
             const int k0 = max(0, x - W + 1), k1 = min(x, ncg - 1);
             const int sb = cs[coff + k0], len = cs[coff + k1 + 1] - sb;
@@ -499,9 +505,9 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
                 const float2 cv = spc[s];
                 const float w1 = pw1[rec.y * W + x - (rec.x & 0xffff)];   // dx in [0, W) for this column range
                 const float cr = cv.x * w1, ci = cv.y * w1;
-                const float4 *wv = reinterpret_cast<const float4 *>(spw2r + s * kRowsReg);
+                const float4 *wv = reinterpret_cast<const float4 *>(spw2r + s * RS);
 #pragma unroll
-                for (int r4 = 0; r4 < kRowsReg / 4; ++r4) {
+                for (int r4 = 0; r4 < RR / 4; ++r4) {
                     const float4 w = wv[r4];
                     ar[4 * r4 + 0] = __builtin_fmaf(cr, w.x, ar[4 * r4 + 0]);
                     ai[4 * r4 + 0] = __builtin_fmaf(ci, w.x, ai[4 * r4 + 0]);
@@ -518,7 +524,7 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
         if (p < np) {
             const int ab = g ? pA * EA + p * EB : p * EA;
 #pragma unroll
-            for (int r = 0; r < kRowsReg; ++r) {
+            for (int r = 0; r < RR; ++r) {
                 if (r < ey) {
                     accr[ab + r * ex + x] = ar[r];
                     acci[ab + r * ex + x] = ai[r];
@@ -539,12 +545,20 @@ __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
             slotp[cell] = make_float2(sr, si);   // the assembly adds the slot to the grid rows it covers
         }
     };
+    typedef std::integral_constant<int, kRowsReg> all_rows;
+    typedef std::integral_constant<int, kRowsLow> low_rows;
     if (nsb == 2) {
-        register_gather(std::true_type{});
+        if (low)
+            register_gather(std::true_type{}, low_rows{});
+        else
+            register_gather(std::true_type{}, all_rows{});
         return;
     }
     if (nparts > 0 && e2 <= kRowsReg) {
-        register_gather(std::false_type{});
+        if (low)
+            register_gather(std::false_type{}, low_rows{});
+        else
+            register_gather(std::false_type{}, all_rows{});
         return;
     }
     if (nparts > 0) {
