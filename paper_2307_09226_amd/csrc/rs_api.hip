@@ -182,8 +182,10 @@ rs_status rs_check_pixels(const rs_plan *pl, const rs_pixels *px)
 // waited for 60-90 us more, as the device's pool
 // unmaps at every synchronisation (4,057-pixel request, waited for: 99 -> 37
 // us; the 65,536-pixel NUFFT frame 197 -> 119 us).
-// Blocks are powers of two, kBlocks of them and kKeepBytes in all at most,
-// and go with the plan.  A call owns its block from take to give, so calls
+// At most kBlocks blocks and kKeepBytes in all; they go with the plan, and a
+// larger call on the stream replaces its block.  Sizes are rounded up by an
+// eighth at most: the runtime maps 2 MiB and more on its own (a first call
+// that needs 1.8 MB: 155 us with a block of 2 MiB, 72 us with 1.9).  A call owns its block from take to give, so calls
 // of several threads have a block each; the event recorded at give is waited
 // for at the next take, which costs nothing on the same stream and keeps a
 // stream that got the handle of a destroyed one behind its work.  Streams do
@@ -191,7 +193,7 @@ rs_status rs_check_pixels(const rs_plan *pl, const rs_pixels *px)
 // block, and every call under capture, uses the device's pool.
 constexpr int kBlocks = 8;
 constexpr size_t kKeepBytes = (size_t)256 << 20;
-constexpr size_t kMinBlock = (size_t)64 << 10;
+constexpr size_t kMinBlock = (size_t)16 << 10;
 
 struct rs_blocks {
     struct block {
@@ -209,24 +211,37 @@ struct rs_blocks {
 
 static rs_blocks::block *block_take(rs_blocks *k, size_t bytes, hipStream_t st)
 {
-    size_t size = kMinBlock;
-    while (size < bytes && size <= kKeepBytes) size <<= 1;
-    rs_blocks::block *x = nullptr;
+    if (bytes > kKeepBytes) return nullptr;
+    size_t step = kMinBlock;   // an eighth of the power of two below
+    while (16 * step <= bytes) step <<= 1;
+    const size_t size = (bytes + step - 1) / step * step;
     std::lock_guard<std::mutex> g(k->m);
+    rs_blocks::block *x = nullptr;   // the stream's largest block
     for (int i = 0; i < k->n; ++i) {
         rs_blocks::block &c = k->b[i];
-        if (!c.taken && c.st == st && c.bytes >= bytes && (!x || c.bytes < x->bytes)) x = &c;
+        if (!c.taken && c.p && c.st == st && (!x || c.bytes > x->bytes)) x = &c;
     }
     if (x) {
         if (hipStreamWaitEvent(st, x->used, 0) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        x->taken = true;
-        return x;
+        if (x->bytes >= bytes) {
+            x->taken = true;
+            return x;
+        }
+        if (k->total - x->bytes + size > kKeepBytes || hipFreeAsync(x->p, st) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        k->total -= x->bytes;
+        x->p = nullptr;
+    } else {
+        for (int i = 0; i < k->n; ++i)   // a place left empty by a failed allocation
+            if (!k->b[i].taken && !k->b[i].p) x = &k->b[i];
+        if (k->total + size > kKeepBytes || (!x && k->n == kBlocks)) return nullptr;
+        if (!x) x = &k->b[k->n++];
     }
-    if (k->n == kBlocks || k->total + size > kKeepBytes) return nullptr;
-    x = &k->b[k->n];
     if (!x->used && hipEventCreateWithFlags(&x->used, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         x->used = nullptr;
@@ -241,7 +256,6 @@ static rs_blocks::block *block_take(rs_blocks *k, size_t bytes, hipStream_t st)
     x->st = st;
     x->taken = true;
     k->total += size;
-    ++k->n;
     return x;
 }
 

@@ -56,3 +56,31 @@ def test_streams_sizes_and_threads(form):
     for i, cube in got:
         assert torch.equal(cube, want[i])
     plan.close()
+
+
+@pytest.mark.parametrize("form", ["mfma", "nufft"])
+def test_captured_calls_keep_their_own_workspace(form):
+    """A call captured after eager ones takes no kept workspace: replays
+    between eager calls on other pixels give the bits of the eager call."""
+    import torch
+    from paper_2307_09226_amd import rs
+    radar = scenes.radar_for(2, 2, 64, 32, Fs=10e6, Tb=40e-6)
+    plan = rs.rs_cube_plan(radar, rs.RS_FORM_MFMA_SPLIT16 if form == "mfma" else rs.RS_FORM_NUFFT,
+                           rs.RS_C64, max_pixels=6001)
+    a, b = (rs.DevicePixels.from_host(scenes.tiny_scene(90 + i, P, vmax=6.0)) for i, P in enumerate((3000, 6001)))
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        want, cube, other = (rs.new_cube(plan, "cuda:0") for _ in range(3))
+        rs.rs_beat_synthesize(plan, a, want, stream=s)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            rs.rs_beat_synthesize(plan, a, cube, stream=s)
+        for _ in range(4):
+            cube.zero_()
+            rs.rs_beat_synthesize(plan, b, other, stream=s)
+            g.replay()
+            rs.rs_beat_synthesize(plan, b, other, stream=s)
+            s.synchronize()
+            assert torch.equal(cube, want)
+    plan.close()
