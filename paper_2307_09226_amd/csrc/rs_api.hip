@@ -259,11 +259,15 @@ static rs_blocks::block *block_take(rs_blocks *k, size_t bytes, hipStream_t st)
     return x;
 }
 
-// The device is idle, or none of the plan's calls is in flight.
+// None of the plan's calls is in flight: the blocks go back to the device's
+// pool, which releases them at the next synchronisation.
 static void blocks_destroy(rs_blocks *k)
 {
     for (int i = 0; i < kBlocks; ++i) {
-        if (k->b[i].p) (void)hipFree(k->b[i].p);
+        if (k->b[i].p && hipFreeAsync(k->b[i].p, nullptr) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipFree(k->b[i].p);
+        }
         if (k->b[i].used) (void)hipEventDestroy(k->b[i].used);
     }
     delete k;
