@@ -215,8 +215,10 @@ __device__ __forceinline__ int4 block_min4(int4 v, int4 *red)
 // No LDS atomics: neighbouring pixels share most of their window, and
 // atomics on the same LDS cells from successive instructions serialise.
 // Under 40 KB of LDS for W <= 7 and under 128 VGPRs: four workgroups per CU.
-// Bound by the vector instructions it issues (71 % of the issue slots over a
-// frame of 65,536 pixels and 12 channels, W = 7).
+// Bound by the vector instructions it issues (0.66 of the issue slots).  A
+// frame of 65,536 pixels and 12 channels, W = 7: 64.7 us and 2,385
+// instructions a wavefront with a rank sort of 256 keys and a gather of 16
+// rows, 49.7 us with the mask sort, 38.9 us and 1,375 with the low gather.
 template <int W>
 __global__ __launch_bounds__(kSpreadThreads) void k_nufft_spread(nu_args A)
 {
