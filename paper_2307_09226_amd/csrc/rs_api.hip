@@ -1,6 +1,7 @@
 // Host side of the C ABI (include/rs.h): plans, single-frame and batched
 // synthesis.  All device work is enqueued on the caller's stream.
 #include "rs_api_internal.h"
+#include "rs_chunks.h"
 
 #include <cerrno>
 #include <cmath>
@@ -33,11 +34,29 @@ namespace {
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
-int64_t round_up(int64_t v, int64_t m) { return ((v + m - 1) / m) * m; }
-
 }  // namespace
 
 // ---------------------------------------------------------------- plans ----
+
+static rs_chunk_rule chunk_rule(const rs_plan *pl)
+{
+    const bool plain = pl->form == RS_FORM_FP64_DIRECT;
+    rs_chunk_rule r;
+    r.items = (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
+    // plain form: chunks for items_target tiles of 64 samples x 64 or 128
+    // blocks whatever the kernel's tile is, so that the workspace of a call
+    // does not depend on it
+    r.tiles = plain ? (int64_t)pl->C * ((pl->Ns + 63) / 64) * (pl->L <= 64 ? 1 : (pl->L + 127) / 128) : r.items;
+    r.items_target = pl->items_target;
+    r.min_chunk = pl->min_chunk;
+    // mirrored pairs: whole pairs of 32-pixel steps (that kernel runs its steps
+    // in pairs)
+    r.step = pl->mirror ? 64 : 16;
+    r.ncu = pl->ncu;
+    r.fine = plain ? 128 : 0;
+    r.cube_bytes = (int64_t)pl->C * pl->L * pl->Ns * (plain ? 16 : 8);
+    return r;
+}
 
 rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *chunk)
 {
@@ -46,41 +65,7 @@ rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *ch
         *chunk = pl->min_chunk;
         return RS_OK;
     }
-    // plain form: chunks for items_target tiles of 64 samples x 64 or 128
-    // blocks whatever the kernel's tile is, so that the workspace of a call
-    // does not depend on it
-    const int64_t tiles = pl->form == RS_FORM_FP64_DIRECT
-                              ? (int64_t)pl->C * ((pl->Ns + 63) / 64) * (pl->L <= 64 ? 1 : (pl->L + 127) / 128)
-                              : (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
-    int64_t s_target = pl->items_target / tiles;
-    if (s_target < 1) s_target = 1;
-    int64_t ch = (P + s_target - 1) / s_target;
-    // mirrored pairs: whole pairs of 32-pixel steps (that kernel runs its
-    // steps in pairs)
-    ch = round_up(ch, pl->mirror ? 64 : 16);
-    if (ch < pl->min_chunk) ch = pl->min_chunk;
-    // Few pixels: where the smallest chunk leaves compute units without a
-    // work item, finer chunks (whole steps), as long as the partial sums stay
-    // within 16 MiB.  A batch forms its frames' sums in the same chunks (its
-    // cubes have the bits of single calls), and there the partial sums only
-    // cost traffic, hence no finer than this.  1 x 4, Ns 128, L 64, 4,057
-    // pixels: 40 us with 4 chunks of 1,024, 29 us with 7 of 640, 23 us with 16
-    // of 256; 200 such frames in a batch: 458, 523 and 795 us.  3 x 4, 256 x
-    // 64, 47 frames of 4,641 pixels: 453, 508, and 654 us with chunks of 512.
-    // Plain form, 2 x 4, 64 x 32, 4,096 pixels: 31.6 us with chunks of 256, 28.7
-    // us with 128 (256 work items).
-    const int64_t fine = pl->mirror ? 640 : (pl->form == RS_FORM_FP64_DIRECT ? 128 : 0);
-    const int64_t items = (int64_t)pl->C * pl->n_tiles * pl->l_tiles;
-    if (fine > 0 && (P + ch - 1) / ch * items < pl->ncu) {
-        const int64_t cube = (int64_t)pl->C * pl->L * pl->Ns * (pl->mirror ? 8 : 16);
-        int64_t s2 = pl->ncu / items;
-        if (s2 > ((int64_t)16 << 20) / cube) s2 = ((int64_t)16 << 20) / cube;
-        if (s2 >= 1) {
-            int64_t c2 = round_up((P + s2 - 1) / s2, pl->mirror ? 64 : 16);
-            if (c2 < fine) c2 = fine;
-            if (c2 < ch) ch = c2;
-        }
-    }
+    const int64_t ch = rs_chunk_pixels(chunk_rule(pl), P);
     if (ch > (int64_t)1 << 30) return rs_fail(RS_E_INVALID, "pixel count too large");
     *chunk = (int32_t)ch;
     *S = (int32_t)((P + ch - 1) / ch);
