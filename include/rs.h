@@ -186,8 +186,8 @@ rs_status rs_cube_plan(const rs_radar *radar, rs_form form, rs_dtype dtype,
 rs_status rs_cube_plan_nufft(const rs_radar *radar, rs_dtype dtype, int64_t max_pixels,
                              double tolerance, rs_plan **out);
 
-/* Bytes of device workspace rs_beat_synthesize_ws needs for P pixels
- * (0 <= P <= max_pixels).  Errors: RS_E_INVALID. */
+/* Bytes of device workspace that serve rs_beat_synthesize_ws for any number of
+ * pixels up to P (0 <= P <= max_pixels).  Errors: RS_E_INVALID. */
 rs_status rs_plan_workspace_bytes(const rs_plan *plan, int64_t P, size_t *bytes);
 
 /* Matrix-core tile configurations are named "WNxTLxNW": a work item covers

@@ -613,19 +613,29 @@ extern "C" void rs_plan_destroy(rs_plan *pl)
     delete pl;
 }
 
-extern "C" rs_status rs_plan_workspace_bytes(const rs_plan *pl, int64_t P, size_t *bytes)
+// Workspace of one call of P pixels.
+static rs_status call_bytes(const rs_plan *pl, int64_t P, size_t *bytes)
 {
-    if (!pl || !bytes) return rs_fail(RS_E_INVALID, "NULL argument");
-    if (P < 0 || P > pl->max_pixels) return rs_fail(RS_E_INVALID, "P out of range");
     if (pl->form == RS_FORM_NUFFT) {
         *bytes = rs_nufft_workspace(pl, P);
         return RS_OK;
     }
     int32_t S, chunk;
-    rs_status s = rs_plan_chunking(pl, P, &S, &chunk);
-    if (s != RS_OK) return s;
-    *bytes = rs_workspace_bytes(pl, S);
-    return RS_OK;
+    const rs_status s = rs_plan_chunking(pl, P, &S, &chunk);
+    if (s == RS_OK) *bytes = rs_workspace_bytes(pl, S);
+    return s;
+}
+
+// What any call of up to P pixels needs: a program sizes its workspace for its
+// largest frame.
+extern "C" rs_status rs_plan_workspace_bytes(const rs_plan *pl, int64_t P, size_t *bytes)
+{
+    if (!pl || !bytes) return rs_fail(RS_E_INVALID, "NULL argument");
+    if (P < 0 || P > pl->max_pixels) return rs_fail(RS_E_INVALID, "P out of range");
+    const rs_status s = call_bytes(pl, P, bytes);
+    if (s == RS_OK && pl->form != RS_FORM_NUFFT && P > 0)
+        *bytes = rs_workspace_bytes(pl, (int32_t)rs_chunk_count_upto(chunk_rule(pl), P));
+    return s;
 }
 
 extern "C" rs_status rs_plan_describe(const rs_plan *pl, int64_t P, char *buf, size_t len)
@@ -865,7 +875,7 @@ extern "C" rs_status rs_beat_synthesize(rs_plan *pl, const rs_pixels *px, void *
     rs_status s = rs_check_pixels(pl, px);
     if (s != RS_OK) return s;
     size_t need = 0;
-    if ((s = rs_plan_workspace_bytes(pl, px->P, &need)) != RS_OK) return s;
+    if ((s = call_bytes(pl, px->P, &need)) != RS_OK) return s;
     device_guard g(pl->device);
     if (g.st != RS_OK) return g.st;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
@@ -919,7 +929,7 @@ extern "C" rs_status rs_beat_synthesize_noalloc(rs_plan *pl, const rs_pixels *px
     rs_status s = rs_check_pixels(pl, px);
     if (s != RS_OK) return s;
     size_t need = 0;
-    if ((s = rs_plan_workspace_bytes(pl, px->P, &need)) != RS_OK) return s;
+    if ((s = call_bytes(pl, px->P, &need)) != RS_OK) return s;
     if (need > (size_t)RS_STATIC_SCRATCH_BYTES)
         return rs_fail(RS_E_INVALID,
                        "workspace of %zu bytes exceeds the static scratch of %zu bytes (P = %lld): use "

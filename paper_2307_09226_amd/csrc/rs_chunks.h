@@ -44,3 +44,28 @@ inline int64_t rs_chunk_pixels(const rs_chunk_rule &r, int64_t P)
     }
     return ch;
 }
+
+inline int64_t rs_chunk_count(const rs_chunk_rule &r, int64_t P)
+{
+    const int64_t ch = rs_chunk_pixels(r, P);
+    return (P + ch - 1) / ch;
+}
+
+// The most chunks that any pixel count up to P > 0 is cut into.  The count
+// itself falls here and there as P grows: from 1,024 s pixels on, s chunks become
+// fewer by the rounding of their size, and where finer chunks end.
+inline int64_t rs_chunk_count_upto(const rs_chunk_rule &r, int64_t P)
+{
+    int64_t s = r.items_target / r.tiles;
+    if (s < 1) s = 1;
+    int64_t most = (P + r.min_chunk - 1) / r.min_chunk;   // reached up to P = s min_chunk
+    if (most > s) most = s;
+    if (r.fine > 0 && r.items < r.ncu) {
+        int64_t s2 = r.ncu / r.items;
+        if (s2 > ((int64_t)16 << 20) / r.cube_bytes) s2 = ((int64_t)16 << 20) / r.cube_bytes;
+        const int64_t f = (P + r.fine - 1) / r.fine;       // reached up to P = s2 fine
+        if (f < s2) s2 = f;
+        if (s2 > most) most = s2;
+    }
+    return most;
+}

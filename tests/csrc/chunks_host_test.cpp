@@ -6,12 +6,6 @@
 #include <cstdlib>
 #include <initializer_list>
 
-static int64_t chunks(const rs_chunk_rule &r, int64_t P)
-{
-    const int64_t ch = rs_chunk_pixels(r, P);
-    return (P + ch - 1) / ch;
-}
-
 #define CHECK(cond)                                                                       \
     do {                                                                                  \
         if (!(cond)) {                                                                    \
@@ -46,13 +40,35 @@ static rs_chunk_rule plain(int64_t items, int64_t tiles)
     return r;
 }
 
+// The bound for every pixel count up to P is the largest count seen so far.
+static void sweep_bound(const rs_chunk_rule &r)
+{
+    int64_t most = 0;
+    for (int64_t P = 1; P < 600000; ++P) {
+        const int64_t S = rs_chunk_count(r, P);
+        if (S > most) most = S;
+        if (P < 5000 || P % 64 < 2) CHECK(rs_chunk_count_upto(r, P) == most);
+    }
+}
+
 int main()
 {
+    for (int64_t items : {1, 3, 4, 12, 64, 300}) {
+        for (int64_t step : {16, 64}) sweep_bound(matrix_core(items, step));
+        sweep_bound(plain(items, items));
+        sweep_bound(plain(items, 2 * items));
+        sweep_bound(plain(2 * items, items));
+        rs_chunk_rule r = plain(items, items);
+        r.cube_bytes = (int64_t)3 << 20;   // finer chunks stop at 16 MiB
+        sweep_bound(r);
+        r.cube_bytes = (int64_t)17 << 20;
+        sweep_bound(r);
+    }
     for (int64_t items : {1, 2, 4, 12, 21, 64, 100, 300})
         for (int64_t step : {16, 64}) {
             const rs_chunk_rule r = matrix_core(items, step);
             for (int64_t P = 1; P < 400000; P += P < 3000 ? 1 : 997) {
-                const int64_t ch = rs_chunk_pixels(r, P), S = chunks(r, P);
+                const int64_t ch = rs_chunk_pixels(r, P), S = rs_chunk_count(r, P);
                 CHECK(ch % step == 0 && ch * S >= P && ch * (S - 1) < P);
                 // a request holds no more partial sums than 1,024-pixel chunks
                 // make, so a session of small requests admits as many of them
@@ -64,7 +80,7 @@ int main()
         for (int64_t tiles : {items, 4 * items}) {
             const rs_chunk_rule r = plain(items, tiles);
             for (int64_t P = 1; P < 300000; P += P < 3000 ? 1 : 997) {
-                const int64_t ch = rs_chunk_pixels(r, P), S = chunks(r, P);
+                const int64_t ch = rs_chunk_pixels(r, P), S = rs_chunk_count(r, P);
                 CHECK(ch % 16 == 0 && ch >= 128 && ch * S >= P && ch * (S - 1) < P);
                 CHECK(ch >= 256 || S * r.cube_bytes <= (int64_t)16 << 20);
             }
