@@ -6,8 +6,8 @@
 //   X_c[k][d] = sum_l sum_n Y[c][l][n] exp(-j2pi k n / Ns) exp(+j2pi d l / L)
 //   power[k][d] = sum_c |X_c[k][d]|^2
 //
-// Fused path (Ns = 256, L = 16 D2 with D2 in {4, 8}, many frames: see
-// rd_fused_pays): one workgroup
+// Fused path (Ns = 256, L = 16 D2 with D2 in {2, 4, 8}, many frames: see
+// rs_rd_fused_pays): one workgroup
 // holds a whole channel's L x 256 tile in registers, 64 entries a thread
 // (4 rows of 16), and takes it through both FFTs without touching HBM in
 // between:
@@ -28,11 +28,12 @@
 // HBM traffic: the cubes read once, plus one partial map per (workgroup,
 // frame) written and read back, plus the map.
 //
-// Two-pass path (other shapes):
+// Two-pass path (other shapes; rs_rd_range_in_registers and
+// rs_rd_doppler_in_registers choose the kernels of each pass):
 //   k_range_reg      fast-time FFT of every (frame, channel, block) row in
 //                    registers (16 points a thread, 16 x 16 x M factors,
 //                    exchanged through LDS inside one wavefront) ->
-//                    rf[F][C][L][Ns] (float2 workspace); Ns 16..1024
+//                    rf[F][C][L][Ns] (float2 workspace); Ns 64..1024
 //   k_doppler_reg    per (frame, group of range bins, run of channels): the
 //                    inverse-sign FFT over blocks as 16 x M in registers and
 //                    one LDS exchange, |.|^2 summed in registers over the
@@ -43,32 +44,32 @@
 // The runs fill the chip: one 192-channel cube of 512 x 64 has 8 groups of
 // range bins, so a workgroup per group that loops over all channels used 8
 // to 32 of 256 compute units (0.577 ms; 0.044 ms in runs).
-//   k_range_fft, k_doppler_power   the same two passes for the remaining
-//                    lengths (Ns < 16 or > 1024, L < 16 or > 256): iterative
-//                    radix-2 FFTs in LDS, a workgroup per row group and per
-//                    group of range bins
+//   k_range_fft, k_doppler_power   the same two passes for the other lengths
+//                    (Ns < 64 or > 1024; L < 16 or > 256) and for few channels:
+//                    iterative radix-2 FFTs in LDS, a workgroup per row group
+//                    and per group of range bins
 // All paths compute in float32 with twiddles evaluated in binary64 and are
 // deterministic (fixed operation and summation order).
 #include "rs_api_internal.h"
 #include "rs_fft.h"
+#include "rs_rd_layout.h"
 
 #include <cmath>
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kRdThreads;
 constexpr int kMaxPerThread = 16;   // power elements per thread in k_doppler_power
-constexpr int kGroupElems = 4096;   // KB * L, at most (dynamic LDS <= 64 KiB)
 // k_range_reg workgroups per compute unit (192 channels of 512 x 64: 44.0 us a
 // call with 2, 45.3 with 4, 50.5 with 8; 10 frames of 8 x 1024 x 64: 42.3, 46.9,
-// 46.6), and k_doppler_reg workgroups per compute unit aimed at (192 channels
-// of 512 x 256: 131 us with 1, 126 with 2, 133 with 4)
-constexpr int kRangePerCu = 2, kDopplerPerCu = 2;
+// 46.6)
+constexpr int kRangePerCu = 2;
 
 struct rd_peak_part {
     float v;
     int32_t idx;   // k * L + d, -1 when the group has no eligible cell
 };
+static_assert(sizeof(rd_peak_part) == kRdPeakPartBytes, "as the layout counts it");
 
 template <typename IT>
 __device__ __forceinline__ float2 load_c(const IT *p) { return make_float2((float)p->x, (float)p->y); }
@@ -179,12 +180,9 @@ __global__ __launch_bounds__(kThreads) void k_doppler_power(const float2 *rf, fl
 // ---------------------------------------------------------------------------
 // Fused path
 // ---------------------------------------------------------------------------
-constexpr int kFNs = 256;                 // fast-time length of the fused path
 constexpr int kFR = 16;                   // 256 = 16 x 16
 constexpr int kFHalf = kFNs / 2;          // range bins per slow-time half
 constexpr int kFX1 = kFR * (kFR + 1);     // one row of the fast-time transpose (padded, = 16 mod 32)
-constexpr int kMergeCells = 4096;         // cells per k_rd_merge workgroup (256 threads, 4 float4 each)
-constexpr int kMapCells = 256;            // cells per k_map_merge workgroup
 constexpr int kFusedRows = 4;             // tile rows a thread holds (64 entries)
 
 // cos(2 pi m / 16), m taken modulo 16
@@ -278,7 +276,7 @@ struct range_shape {
     // LDS of a row: the transpose [k1][q] with an odd stride, then (three
     // factors) [k2a][q0][k1] with 16 slots of padding per k2a
     static constexpr int X = T > 16 ? 16 * (T + 16) : 16 * (T + 1);
-    static_assert(LOGN >= 4 && LOGN <= 10, "one wavefront holds a row");
+    static_assert(LOGN >= 6 && LOGN <= 10, "one wavefront holds a row");
 };
 
 // Fast-time FFT, row by row: n = q + T n1, 16-point DFT over n1 -> k1, times
@@ -387,7 +385,7 @@ __global__ __launch_bounds__(kThreads) void k_doppler_reg(const float2 *__restri
     const int DS = M * KB + (M == 16 ? 16 : 0), CPS = 16 * DS;   // CP CPS <= the array (M = 16: CP = 1)
     const int tid = threadIdx.x;
     const int k = tid & (KB - 1), j = (tid >> logkb) & (M - 1), cp = tid >> (logkb + LOGM);
-    const int groups = Ns >> logkb, sblk = S / CP;
+    const int groups = Ns >> logkb, sblk = (S + CP - 1) / CP;
     const int s = (int)(blockIdx.x % sblk) * CP + cp;
     const int fg = (int)(blockIdx.x / sblk);
     const int f = fg / groups, k0 = (fg % groups) << logkb;
@@ -439,6 +437,7 @@ __global__ __launch_bounds__(kThreads) void k_doppler_reg(const float2 *__restri
 #pragma unroll
         for (int d2 = 0; d2 < M; ++d2) sm[k * (L + 1) + E * j + e + 16 * d2] = acc[e * M + d2];
     __syncthreads();
+    if (s >= S) return;   // beyond the last run
     const int lt = tid & (M * KB - 1);
     float *dst = slots + (((int64_t)f * S + s) * Ns + k0) * L;
 #pragma unroll
@@ -823,18 +822,6 @@ int ilog2_exact(int v)
     return l;
 }
 
-// Workgroups of the fused path: at most one per compute unit (a
-// workgroup's LDS fills one), as few as keep the longest run at
-// ceil(F C / compute units) items, the items split evenly over them; a
-// frame's items can fall into several runs, whose partial maps k_rd_merge
-// adds (fewer workgroups, fewer partial maps).
-int64_t rd_fused_workgroups(int64_t nframes, int C, int ncu)
-{
-    const int64_t n = nframes * C;
-    const int64_t per = (n + ncu - 1) / std::max(1, ncu);
-    return std::max<int64_t>(1, (n + per - 1) / per);
-}
-
 template <typename IT>
 void launch_range_reg(int logn, const void *cubes, float2 *rf, int64_t rows, int ncu, hipStream_t st)
 {
@@ -842,8 +829,6 @@ void launch_range_reg(int logn, const void *cubes, float2 *rf, int64_t rows, int
     const int64_t groups = (rows * (int64_t)((1 << logn) / 16) + kThreads - 1) / kThreads;
     const dim3 grid((unsigned)std::min<int64_t>(groups, (int64_t)ncu * kRangePerCu));
     switch (logn) {
-    case 4: hipLaunchKernelGGL((k_range_reg<4, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
-    case 5: hipLaunchKernelGGL((k_range_reg<5, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
     case 6: hipLaunchKernelGGL((k_range_reg<6, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
     case 7: hipLaunchKernelGGL((k_range_reg<7, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
     case 8: hipLaunchKernelGGL((k_range_reg<8, IT>), grid, dim3(kThreads), 0, st, src, rf, rows); break;
@@ -882,84 +867,25 @@ template <typename IT>
 hipError_t launch_fused_l(int L, const void *cubes, float *slots, int C, int64_t nitems, int W, int J,
                           hipStream_t st)
 {
-    return L == 64 ? launch_fused<4, IT>(cubes, slots, C, nitems, W, J, st)
-                   : launch_fused<8, IT>(cubes, slots, C, nitems, W, J, st);
+    switch (L) {
+    case 32: return launch_fused<2, IT>(cubes, slots, C, nitems, W, J, st);
+    case 64: return launch_fused<4, IT>(cubes, slots, C, nitems, W, J, st);
+    default: return launch_fused<8, IT>(cubes, slots, C, nitems, W, J, st);
+    }
 }
 
 }  // namespace
 
 namespace {
 
-// Workspace of one call, in 256-byte aligned pieces.  Fused path: the
-// partial maps [W][J][cells], the map when the caller wants none, the block
-// maxima.  Two-pass path: the float2 fast-time spectra, the runs' partial
-// maps [F][S][cells] (L 16..256), the map when the caller wants none, the
-// group maxima.
-struct rd_layout {
-    bool fused = false;
-    int64_t W = 0, J = 0, nitems = 0;
-    int groups = 0, kb = 0;
-    int S = 0, per = 0, logkb = 0;   // channel runs of k_doppler_reg (S = 0: k_doppler_power)
-    size_t mid = 0, slots = 0, pw = 0, parts = 0, total = 0;   // byte offsets / sizes
-};
-
-// Whether the fused path is the faster one: it reads the cubes once (the
-// two-pass path moves three times the bytes) but runs one workgroup per
-// compute unit, one channel at a time, and merges a partial map per workgroup
-// and frame, so it needs enough (frame, channel, block) rows, and frames of
-// which few workgroups share one.  Measured, fused / two-pass in us (C, L,
-// frames): 12, 128: 1: 33.2 / 20.4, 10: 36.6 / 32.7, 16: 40.5 / 40.7, 32: 57 / 65,
-// 100: 136 / 216; 4, 128: 40: 36 / 42; 8, 64: 32: 31 / 33; 192, 128: 1: 122 / 41,
-// 2: 97 / 62, 4: 106 / 113; 12, 32: 30: 34 / 29; 12, 16: 100: 58 / 34.
-bool rd_fused_pays(int64_t nframes, int C, int Ns, int L)
+rs_rd_shape rd_shape(const rs_plan *pl)
 {
-    const int64_t rows = nframes * C * L;
-    return Ns == kFNs && L >= 64 && L <= 128 && ((nframes >= 16 && rows >= 16384) || rows >= 98304);
-}
-
-rd_layout rd_plan_layout(const rs_plan *pl, int64_t nframes, bool power_given)
-{
-    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    rd_layout y;
-    const int Ns = pl->Ns, L = pl->L, C = pl->C;
-    const int64_t cells = (int64_t)Ns * L;
-    y.fused = rd_fused_pays(nframes, C, Ns, L);
-    size_t mid_bytes, slot_bytes = 0;
-    if (y.fused) {
-        y.nitems = nframes * C;
-        y.W = rd_fused_workgroups(nframes, C, pl->ncu);
-        const int64_t per = (y.nitems + y.W - 1) / y.W;
-        y.J = (per - 1 + C - 1) / C + 1;   // frames a run of `per` items can touch
-        y.groups = (int)(cells / kMergeCells);
-        mid_bytes = (size_t)(y.W * y.J * cells) * sizeof(float);
-    } else {
-        y.kb = std::min(std::min(16, kGroupElems / L), Ns);
-        y.groups = Ns / y.kb;
-        mid_bytes = (size_t)(nframes * C * L * Ns) * sizeof(float2);
-        if (L >= 16 && L <= 256 && Ns >= 16) {
-            // KB range bins x L / 16 threads per channel, CP channels side by
-            // side; enough runs of channels for kDopplerPerCu workgroups per
-            // compute unit
-            const int kb = std::min(Ns, kThreads * 16 / L), cp = kThreads / (kb * (L / 16));
-            y.logkb = __builtin_ctz((unsigned)kb);
-            const int64_t base = nframes * (Ns / kb);
-            int64_t blocks = ((int64_t)pl->ncu * kDopplerPerCu + base - 1) / base;
-            blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, (C + cp - 1) / cp));
-            y.per = (int)((C + blocks * cp - 1) / (blocks * cp));
-            y.S = (int)((C + (int64_t)y.per * cp - 1) / ((int64_t)y.per * cp)) * cp;
-            y.groups = (int)(cells / kMapCells);
-            // one run: its map is the frame's
-            slot_bytes = y.S == 1 ? 0 : (size_t)(nframes * y.S * cells) * sizeof(float);
-        }
-    }
-    const size_t pw_bytes = power_given ? 0 : (size_t)(nframes * cells) * sizeof(float);
-    const size_t part_bytes = (size_t)nframes * y.groups * sizeof(rd_peak_part);
-    y.mid = 0;
-    y.slots = up(mid_bytes);
-    y.pw = y.slots + up(slot_bytes);
-    y.parts = y.pw + up(pw_bytes);
-    y.total = y.parts + up(part_bytes);
-    return y;
+    rs_rd_shape q;
+    q.Ns = pl->Ns;
+    q.L = pl->L;
+    q.C = pl->C;
+    q.ncu = pl->ncu;
+    return q;
 }
 
 // Argument checks of both entry points; nframes = 0 passes (nothing to do).
@@ -978,7 +904,7 @@ rs_status rd_check(const rs_plan *pl, const void *cubes, int32_t nframes, int *l
 }
 
 // The launches of one call on `st` with the workspace `ws` laid out as y.
-rs_status rd_run(const rs_plan *pl, const rd_layout &y, const void *cubes, int32_t nframes, int32_t skip_static,
+rs_status rd_run(const rs_plan *pl, const rs_rd_layout &y, const void *cubes, int32_t nframes, int32_t skip_static,
                  float *power, float *doppler_time, rs_rd_peak *peaks, char *ws, int logn, int logl,
                  hipStream_t st)
 {
@@ -1002,7 +928,7 @@ rs_status rd_run(const rs_plan *pl, const rd_layout &y, const void *cubes, int32
     } else {
         float2 *rf = reinterpret_cast<float2 *>(ws + y.mid);
         const int64_t rows = (int64_t)nframes * C * L;
-        if (Ns >= 16 && Ns <= 1024) {
+        if (rs_rd_range_in_registers(Ns)) {
             if (pl->dtype == RS_C128) launch_range_reg<double2>(logn, cubes, rf, rows, pl->ncu, st);
             else launch_range_reg<float2>(logn, cubes, rf, rows, pl->ncu, st);
         } else {
@@ -1022,7 +948,7 @@ rs_status rd_run(const rs_plan *pl, const rd_layout &y, const void *cubes, int32
             float *slots = y.S == 1 ? pw : reinterpret_cast<float *>(ws + y.slots);
             const int cp = kThreads >> (y.logkb + logl - 4);
             launch_doppler_reg(L, rf, slots, C, Ns, y.logkb, y.S, y.per,
-                               (unsigned)(nframes * (Ns >> y.logkb) * (int64_t)(y.S / cp)), st);
+                               (unsigned)(nframes * (Ns >> y.logkb) * (int64_t)((y.S + cp - 1) / cp)), st);
             e = hipGetLastError();
             if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler launch: %s", hipGetErrorString(e));
             hipLaunchKernelGGL(k_map_merge, dim3((unsigned)(nframes * y.groups)), dim3(256), 0, st, slots, pw, parts, y.S,
@@ -1049,7 +975,7 @@ rs_status rd_run(const rs_plan *pl, const rd_layout &y, const void *cubes, int32
 extern "C" size_t rs_range_doppler_workspace_bytes(const rs_plan *pl, int32_t nframes, int32_t power_given)
 {
     if (!pl || nframes <= 0) return 0;
-    return rd_plan_layout(pl, nframes, power_given != 0).total;
+    return rs_rd_plan_layout(rd_shape(pl), nframes, power_given != 0).total;
 }
 
 extern "C" rs_status rs_range_doppler(rs_plan *pl, const void *cubes, int32_t nframes, int32_t skip_static,
@@ -1061,7 +987,7 @@ extern "C" rs_status rs_range_doppler(rs_plan *pl, const void *cubes, int32_t nf
     device_guard g(pl->device);
     if (g.st != RS_OK) return g.st;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const rd_layout y = rd_plan_layout(pl, nframes, power != nullptr);
+    const rs_rd_layout y = rs_rd_plan_layout(rd_shape(pl), nframes, power != nullptr);
     rs_workspace ws(pl, y.total, st);
     if (!ws.p)
         return rs_fail(RS_E_NOMEM, "stream-ordered workspace allocation of %zu bytes failed", y.total);
@@ -1075,7 +1001,7 @@ extern "C" rs_status rs_range_doppler_ws(rs_plan *pl, const void *cubes, int32_t
     int logn = 0, logl = 0;
     const rs_status c = rd_check(pl, cubes, nframes, &logn, &logl);
     if (c != RS_OK || nframes == 0) return c;
-    const rd_layout y = rd_plan_layout(pl, nframes, power != nullptr);
+    const rs_rd_layout y = rs_rd_plan_layout(rd_shape(pl), nframes, power != nullptr);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return rs_fail(RS_E_INVALID, "workspace is NULL or not 256-byte aligned");
     if (workspace_bytes < y.total)

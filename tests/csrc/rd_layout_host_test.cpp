@@ -1,0 +1,57 @@
+// Host test of the range-Doppler paths and workspace layout
+// (paper_2307_09226_amd/csrc/rs_rd_layout.h), built with g++ under the
+// sanitizers.  Prints "ALL OK" and exits 0 on success.
+#include "rs_rd_layout.h"
+
+#include <cstdio>
+#include <cstdlib>
+#include <initializer_list>
+
+#define CHECK(cond)                                                                                          \
+    do {                                                                                                     \
+        if (!(cond)) {                                                                                       \
+            std::fprintf(stderr, "%s:%d: CHECK failed: %s (C %d Ns %d L %d F %lld)\n", __FILE__, __LINE__, #cond, \
+                         q.C, q.Ns, q.L, (long long)F);                                                      \
+            std::exit(1);                                                                                    \
+        }                                                                                                    \
+    } while (0)
+
+template <typename F>
+static void for_shapes(F &&f)
+{
+    for (int Ns = 2; Ns <= 4096; Ns *= 2)
+        for (int L = 2; L <= 1024; L *= 2)
+            for (int C : {1, 2, 3, 4, 5, 8, 12, 31, 64, 97, 192, 1000}) {
+                rs_rd_shape q;
+                q.Ns = Ns;
+                q.L = L;
+                q.C = C;
+                q.ncu = 256;
+                f(q);
+            }
+}
+
+// The runs of a frame's channels: every run has channels, all of them are in
+// one, and their maps take no more than half of the spectra's bytes.
+static void runs(const rs_rd_shape &q)
+{
+    for (int64_t F : {1, 2, 3, 7, 16, 40, 100, 333, 1000, 5000, 20000}) {
+        const rs_rd_layout y = rs_rd_plan_layout(q, F, true);
+        if (y.fused) {
+            CHECK(q.Ns == 256 && y.W <= q.ncu && y.W * y.J >= F);
+            continue;
+        }
+        CHECK(y.groups >= 1 && y.kb * q.L <= kGroupElems);
+        if (!y.S) continue;
+        CHECK((int64_t)y.S * y.per >= q.C && (int64_t)(y.S - 1) * y.per < q.C);
+        CHECK(y.S == 1 || y.pw - y.slots <= (y.slots - y.mid) / 2 + 256);
+        CHECK(q.Ns * (int64_t)q.L % kMapCells == 0);
+    }
+}
+
+int main()
+{
+    for_shapes(runs);
+    std::puts("ALL OK");
+    return 0;
+}

@@ -1,0 +1,36 @@
+"""Range-Doppler maps on both sides of the lines between the paths: few
+channels (LDS Doppler pass), runs side by side of which the last group is
+ragged, many frames, and the fused kernel at L = 32 and few channels."""
+import pytest
+
+from paper_2307_09226_amd import scenes
+from test_rd_gpu import check_rd_frames
+from test_rd_shapes import _cubes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,Ns,L,F,dtype", [
+    (1, 64, 64, 300, 0), (1, 16, 16, 700, 1), (2, 128, 32, 40, 0), (2, 1024, 256, 1, 0),
+    (3, 64, 16, 600, 0), (5, 32, 64, 2, 0), (4, 32, 16, 500, 1), (1, 256, 16, 130, 0), (3, 2048, 32, 3, 0),
+    (1, 256, 32, 143, 0), (1, 256, 32, 144, 0), (3, 256, 32, 60, 1), (2, 256, 64, 47, 0), (2, 256, 64, 48, 0),
+    (1, 256, 128, 96, 0),
+])
+def test_paths(N, Ns, L, F, dtype):
+    """Frames at the ends and in between against the oracle, and the bits of the
+    workspace form."""
+    import torch
+    from paper_2307_09226_amd import rs
+    radar = scenes.radar_for(1, N, Ns, L, Fs=10e6, Tb=40e-6)
+    plan = rs.rs_cube_plan(radar, rs.RS_FORM_MFMA_SPLIT16, dtype, max_pixels=16)
+    cubes = _cubes(radar, F, dtype, 17 + Ns + L)
+    frames = sorted({0, 1 % F, F // 3, F // 2, F - 2 if F > 1 else 0, F - 1})
+    for skip in (True, False):
+        check_rd_frames(radar, plan, cubes, frames, skip_static=skip)
+    power, dtime, _ = rs.range_doppler(plan, cubes)
+    p2, d2 = torch.empty_like(power), torch.empty_like(dtime)
+    ws = torch.empty(rs.rs_range_doppler_workspace_bytes(plan, F, True), dtype=torch.uint8, device="cuda:0")
+    rs.rs_range_doppler_ws(plan, cubes, True, p2, d2, None, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(power, p2) and torch.equal(dtime, d2)
+    plan.close()
