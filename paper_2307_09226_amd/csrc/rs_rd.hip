@@ -903,6 +903,49 @@ rs_status rd_check(const rs_plan *pl, const void *cubes, int32_t nframes, int *l
     return RS_OK;
 }
 
+// Both passes of `nframes` frames (at most y.group) from their first cube on.
+rs_status rd_two_pass(const rs_plan *pl, const rs_rd_layout &y, const void *cubes, int64_t nframes, int32_t skip_static,
+                      float *power, rd_peak_part *parts, char *ws, int logn, int logl, hipStream_t st)
+{
+    const int Ns = pl->Ns, L = pl->L, C = pl->C;
+    const int64_t cells = (int64_t)Ns * L;
+    float2 *rf = reinterpret_cast<float2 *>(ws + y.mid);
+    const int64_t rows = nframes * C * L;
+    if (rs_rd_range_in_registers(Ns)) {
+        if (pl->dtype == RS_C128) launch_range_reg<double2>(logn, cubes, rf, rows, pl->ncu, st);
+        else launch_range_reg<float2>(logn, cubes, rf, rows, pl->ncu, st);
+    } else {
+        const int rpw = std::max(1, 2048 / Ns);
+        const int64_t g1 = (rows + rpw - 1) / rpw;
+        const size_t lds1 = (size_t)(Ns / 2 + rpw * Ns) * sizeof(float2);
+        if (pl->dtype == RS_C128)
+            hipLaunchKernelGGL(k_range_fft<double2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
+                               reinterpret_cast<const double2 *>(cubes), rf, rows, logn, rpw);
+        else
+            hipLaunchKernelGGL(k_range_fft<float2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
+                               reinterpret_cast<const float2 *>(cubes), rf, rows, logn, rpw);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "range FFT launch: %s", hipGetErrorString(e));
+    if (y.S > 0) {
+        float *slots = y.S == 1 ? power : reinterpret_cast<float *>(ws + y.slots);
+        const int cp = kThreads >> (y.logkb + logl - 4);
+        launch_doppler_reg(L, rf, slots, C, Ns, y.logkb, y.S, y.per,
+                           (unsigned)(nframes * (Ns >> y.logkb) * (int64_t)((y.S + cp - 1) / cp)), st);
+        e = hipGetLastError();
+        if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler launch: %s", hipGetErrorString(e));
+        hipLaunchKernelGGL(k_map_merge, dim3((unsigned)(nframes * y.groups)), dim3(256), 0, st, slots, power, parts, y.S,
+                           y.groups, (int)cells, L, skip_static ? 1 : 0);
+    } else {
+        const size_t lds2 = (size_t)(L / 2 + y.kb * L) * sizeof(float2);
+        hipLaunchKernelGGL(k_doppler_power, dim3((unsigned)(nframes * y.groups)), dim3(kThreads), lds2, st, rf, power,
+                           parts, C, logl, Ns, y.kb, skip_static ? 1 : 0);
+    }
+    e = hipGetLastError();
+    if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler map launch: %s", hipGetErrorString(e));
+    return RS_OK;
+}
+
 // The launches of one call on `st` with the workspace `ws` laid out as y.
 rs_status rd_run(const rs_plan *pl, const rs_rd_layout &y, const void *cubes, int32_t nframes, int32_t skip_static,
                  float *power, float *doppler_time, rs_rd_peak *peaks, char *ws, int logn, int logl,
@@ -926,40 +969,12 @@ rs_status rd_run(const rs_plan *pl, const rs_rd_layout &y, const void *cubes, in
         e = hipGetLastError();
         if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "map merge launch: %s", hipGetErrorString(e));
     } else {
-        float2 *rf = reinterpret_cast<float2 *>(ws + y.mid);
-        const int64_t rows = (int64_t)nframes * C * L;
-        if (rs_rd_range_in_registers(Ns)) {
-            if (pl->dtype == RS_C128) launch_range_reg<double2>(logn, cubes, rf, rows, pl->ncu, st);
-            else launch_range_reg<float2>(logn, cubes, rf, rows, pl->ncu, st);
-        } else {
-            const int rpw = std::max(1, 2048 / Ns);
-            const int64_t g1 = (rows + rpw - 1) / rpw;
-            const size_t lds1 = (size_t)(Ns / 2 + rpw * Ns) * sizeof(float2);
-            if (pl->dtype == RS_C128)
-                hipLaunchKernelGGL(k_range_fft<double2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
-                                   reinterpret_cast<const double2 *>(cubes), rf, rows, logn, rpw);
-            else
-                hipLaunchKernelGGL(k_range_fft<float2>, dim3((unsigned)g1), dim3(kThreads), lds1, st,
-                                   reinterpret_cast<const float2 *>(cubes), rf, rows, logn, rpw);
+        for (int64_t f0 = 0; f0 < nframes; f0 += y.group) {
+            const rs_status s = rd_two_pass(pl, y, static_cast<const char *>(cubes) + f0 * C * cells * (pl->dtype == RS_C128 ? 16 : 8),
+                                            std::min(y.group, nframes - f0), skip_static, pw + f0 * cells,
+                                            parts + f0 * y.groups, ws, logn, logl, st);
+            if (s != RS_OK) return s;
         }
-        e = hipGetLastError();
-        if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "range FFT launch: %s", hipGetErrorString(e));
-        if (y.S > 0) {
-            float *slots = y.S == 1 ? pw : reinterpret_cast<float *>(ws + y.slots);
-            const int cp = kThreads >> (y.logkb + logl - 4);
-            launch_doppler_reg(L, rf, slots, C, Ns, y.logkb, y.S, y.per,
-                               (unsigned)(nframes * (Ns >> y.logkb) * (int64_t)((y.S + cp - 1) / cp)), st);
-            e = hipGetLastError();
-            if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler launch: %s", hipGetErrorString(e));
-            hipLaunchKernelGGL(k_map_merge, dim3((unsigned)(nframes * y.groups)), dim3(256), 0, st, slots, pw, parts, y.S,
-                               y.groups, (int)cells, L, skip_static ? 1 : 0);
-        } else {
-            const size_t lds2 = (size_t)(L / 2 + y.kb * L) * sizeof(float2);
-            hipLaunchKernelGGL(k_doppler_power, dim3((unsigned)(nframes * y.groups)), dim3(kThreads), lds2, st, rf, pw,
-                               parts, C, logl, Ns, y.kb, skip_static ? 1 : 0);
-        }
-        e = hipGetLastError();
-        if (e != hipSuccess) return rs_fail(RS_E_DEVICE, "Doppler map launch: %s", hipGetErrorString(e));
     }
     if (peaks || doppler_time) {
         hipLaunchKernelGGL(k_rd_peak, dim3((unsigned)nframes), dim3(kThreads), 0, st, parts, pw, y.groups, Ns, L, rpb,

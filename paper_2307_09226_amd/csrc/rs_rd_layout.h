@@ -16,6 +16,15 @@ constexpr size_t kRdPeakPartBytes = 8;
 // 256: 131 us with 1, 126 with 2, 133 with 4)
 constexpr int kDopplerPerCu = 2;
 
+// Bytes of fast-time spectra that the two-pass path holds at once (a frame's at
+// least); more frames go through it in rounds, so that neither the workspace nor
+// a launch's grid grows with the call.  A round costs its launches' tails (63
+// frames of 192 x 512 x 64: 1.79 ms in one, 2.00 in seven), hence 2 GiB.  At
+// 256 x 16 and 256 x 32 one workgroup could hold a channel without any spectra:
+// there no more than a plan keeps for its allocating calls, at the same speed
+// (8,138 frames of 12 x 256 x 16: 2.03 ms with 3 GiB, 2.04 with 256 MiB).
+inline int64_t rs_rd_spectra_bytes(int Ns, int L) { return Ns == kFNs && L <= 32 ? (int64_t)240 << 20 : (int64_t)2 << 30; }
+
 struct rs_rd_shape {
     int Ns = 0, L = 0, C = 0, ncu = 1;
 };
@@ -82,13 +91,14 @@ inline int64_t rs_rd_fused_workgroups(int64_t nframes, int C, int ncu)
 
 // Workspace of one call, in 256-byte aligned pieces.  Fused path: the
 // partial maps [W][J][cells], the map when the caller wants none, the block
-// maxima.  Two-pass path: the float2 fast-time spectra, the runs' partial
-// maps [F][S][cells] (S > 1), the map when the caller wants none, the
-// group maxima.
+// maxima.  Two-pass path: the float2 fast-time spectra and the runs' partial
+// maps [group][S][cells] (S > 1) of a group of frames, the map when the caller
+// wants none, the group maxima.
 struct rs_rd_layout {
     bool fused = false;
     int64_t W = 0, J = 0, nitems = 0;
-    int groups = 0, kb = 0;
+    int groups = 0, kb = 0;          // maxima per frame; range bins per k_doppler_power workgroup
+    int64_t group = 0;               // frames of one round of the two passes
     int S = 0, per = 0, logkb = 0;   // channel runs of k_doppler_reg (S = 0: k_doppler_power)
     size_t mid = 0, slots = 0, pw = 0, parts = 0, total = 0;   // byte offsets / sizes
 };
@@ -112,21 +122,25 @@ inline rs_rd_layout rs_rd_plan_layout(const rs_rd_shape &q, int64_t nframes, boo
     } else {
         y.kb = std::min(std::min(16, kGroupElems / L), Ns);
         y.groups = Ns / y.kb;
-        mid_bytes = (size_t)(nframes * C * cells) * 8;
-        if (rs_rd_doppler_in_registers(nframes, q)) {
+        const int64_t spectra = C * cells * 8;
+        const int64_t fit = std::min(rs_rd_spectra_bytes(Ns, L) / spectra, ((int64_t)1 << 23) / y.groups);
+        const int64_t most = std::max<int64_t>(1, fit), rounds = (nframes + most - 1) / most;
+        y.group = (nframes + rounds - 1) / rounds;
+        mid_bytes = (size_t)(y.group * spectra);
+        if (rs_rd_doppler_in_registers(y.group, q)) {
             // KB range bins x L / 16 threads per channel, CP channels side by
             // side; enough runs of channels for kDopplerPerCu workgroups per
             // compute unit
             const int kb = std::min(Ns, kRdThreads * 16 / L), cp = kRdThreads / (kb * (L / 16));
             while ((1 << y.logkb) < kb) ++y.logkb;
-            const int64_t base = nframes * (Ns / kb);
+            const int64_t base = y.group * (Ns / kb);
             int64_t blocks = ((int64_t)q.ncu * kDopplerPerCu + base - 1) / base;
             blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, (C + cp - 1) / cp));
             y.per = (int)((C + blocks * cp - 1) / (blocks * cp));
             y.S = (C + y.per - 1) / y.per;
             y.groups = (int)(cells / kMapCells);
             // one run: its map is the frame's
-            slot_bytes = y.S == 1 ? 0 : (size_t)(nframes * y.S * cells) * sizeof(float);
+            slot_bytes = y.S == 1 ? 0 : (size_t)(y.group * y.S * cells) * sizeof(float);
         }
     }
     const size_t pw_bytes = power_given ? 0 : (size_t)(nframes * cells) * sizeof(float);

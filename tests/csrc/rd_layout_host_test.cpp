@@ -35,13 +35,21 @@ static void for_shapes(F &&f)
 // one, and their maps take no more than half of the spectra's bytes.
 static void runs(const rs_rd_shape &q)
 {
-    for (int64_t F : {1, 2, 3, 7, 16, 40, 100, 333, 1000, 5000, 20000}) {
+    for (int64_t F : {1, 2, 3, 7, 16, 40, 100, 333, 1000, 5000, 20000, 300000, 20000000}) {
         const rs_rd_layout y = rs_rd_plan_layout(q, F, true);
         if (y.fused) {
             CHECK(q.Ns == 256 && y.W <= q.ncu && y.W * y.J >= F);
             continue;
         }
         CHECK(y.groups >= 1 && y.kb * q.L <= kGroupElems);
+        // rounds of frames: workspace and grids do not grow with the call (a
+        // frame's own size, and the maxima, aside)
+        const int64_t cells = (int64_t)q.Ns * q.L, frame = 8 * cells * q.C;
+        CHECK(y.group >= 1 && y.group <= F);
+        CHECK(y.group == 1 || y.group * frame <= ((int64_t)2 << 30));
+        CHECK(y.parts <= (size_t)std::max<int64_t>((int64_t)2 << 30, frame) * 3 / 2 + 512);
+        CHECK(q.Ns != 256 || q.L > 32 || y.group == 1 || y.total <= ((size_t)256 << 20) + (size_t)F * y.groups * 8);
+        CHECK(y.group == 1 || y.group * std::max<int64_t>(y.groups, cells / 256) * 256 < ((int64_t)1 << 32));
         if (!y.S) continue;
         CHECK((int64_t)y.S * y.per >= q.C && (int64_t)(y.S - 1) * y.per < q.C);
         CHECK(y.S == 1 || y.pw - y.slots <= (y.slots - y.mid) / 2 + 256);

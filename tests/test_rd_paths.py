@@ -34,3 +34,21 @@ def test_paths(N, Ns, L, F, dtype):
     torch.cuda.synchronize()
     assert torch.equal(power, p2) and torch.equal(dtime, d2)
     plan.close()
+
+
+@pytest.mark.parametrize("N,Ns,L,F", [(12, 256, 16, 641), (2, 1024, 64, 2049), (1, 256, 256, 4097)])
+def test_rounds_of_frames(N, Ns, L, F):
+    """One frame more than a round of the two passes holds (240 MiB of spectra at
+    256 x 16, else 2 GiB): the frames at both ends of both rounds against the
+    oracle, and a workspace that does not grow with the call."""
+    import torch
+    from paper_2307_09226_amd import rs
+    radar = scenes.radar_for(1, N, Ns, L, Fs=10e6, Tb=40e-6)
+    plan = rs.rs_cube_plan(radar, rs.RS_FORM_MFMA_SPLIT16, rs.RS_C64, max_pixels=16)
+    need = [rs.rs_range_doppler_workspace_bytes(plan, n, True) for n in (F - 1, F, 50 * F)]
+    assert need[1] <= need[0] and need[2] <= need[0] + 50 * F * (Ns * L // 256) * 8 + 256
+    g = torch.Generator(device="cuda:0").manual_seed(F)
+    cubes = torch.view_as_complex(torch.randn((F, N, L, Ns, 2), generator=g, device="cuda:0"))
+    h = (F + 1) // 2
+    check_rd_frames(radar, plan, cubes, [0, 1, h - 1, h, h + 1, F - 1], skip_static=True)
+    plan.close()
