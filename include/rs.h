@@ -488,7 +488,7 @@ typedef struct {
 rs_status rs_range_doppler(rs_plan *plan, const void *cubes, int32_t nframes, int32_t skip_static,
                            float *power, float *doppler_time, rs_rd_peak *peaks, void *hip_stream);
 
-/* Device bytes of temporary memory that rs_range_doppler uses for
+/* Device bytes of temporary memory that serve a range-Doppler call of up to
  * `nframes` cubes of `plan`, with (power_given = 1) or without a caller's
  * power map; 0 for nframes <= 0 or a NULL plan. */
 size_t rs_range_doppler_workspace_bytes(const rs_plan *plan, int32_t nframes, int32_t power_given);

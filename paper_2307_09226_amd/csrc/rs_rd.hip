@@ -990,7 +990,9 @@ rs_status rd_run(const rs_plan *pl, const rs_rd_layout &y, const void *cubes, in
 extern "C" size_t rs_range_doppler_workspace_bytes(const rs_plan *pl, int32_t nframes, int32_t power_given)
 {
     if (!pl || nframes <= 0) return 0;
-    return rs_rd_plan_layout(rd_shape(pl), nframes, power_given != 0).total;
+    if (ilog2_exact(pl->Ns) < 1 || ilog2_exact(pl->L) < 1 || pl->Ns > 4096 || pl->L > 1024)
+        return rs_rd_plan_layout(rd_shape(pl), nframes, power_given != 0).total;   // no call takes such a plan
+    return rs_rd_workspace_bytes(rd_shape(pl), nframes, power_given != 0);
 }
 
 extern "C" rs_status rs_range_doppler(rs_plan *pl, const void *cubes, int32_t nframes, int32_t skip_static,

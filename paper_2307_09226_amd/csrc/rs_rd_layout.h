@@ -103,6 +103,16 @@ struct rs_rd_layout {
     size_t mid = 0, slots = 0, pw = 0, parts = 0, total = 0;   // byte offsets / sizes
 };
 
+// Range bins of a k_doppler_power workgroup.
+inline int rs_rd_bins(const rs_rd_shape &q) { return std::max(1, std::min(std::min(16, kGroupElems / q.L), q.Ns)); }
+
+// Frames of a full round (a grid stays below 2^32 threads).
+inline int64_t rs_rd_round(const rs_rd_shape &q)
+{
+    const int64_t spectra = (int64_t)q.C * q.Ns * q.L * 8, groups = q.Ns / rs_rd_bins(q);
+    return std::max<int64_t>(1, std::min(rs_rd_spectra_bytes(q.Ns, q.L) / spectra, ((int64_t)1 << 23) / groups));
+}
+
 inline size_t rs_rd_up(size_t b) { return (b + 255) & ~(size_t)255; }
 
 inline rs_rd_layout rs_rd_plan_layout(const rs_rd_shape &q, int64_t nframes, bool power_given)
@@ -120,13 +130,11 @@ inline rs_rd_layout rs_rd_plan_layout(const rs_rd_shape &q, int64_t nframes, boo
         y.groups = (int)(cells / kMergeCells);
         mid_bytes = (size_t)(y.W * y.J * cells) * sizeof(float);
     } else {
-        y.kb = std::min(std::min(16, kGroupElems / L), Ns);
+        y.kb = rs_rd_bins(q);
         y.groups = Ns / y.kb;
-        const int64_t spectra = C * cells * 8;
-        const int64_t fit = std::min(rs_rd_spectra_bytes(Ns, L) / spectra, ((int64_t)1 << 23) / y.groups);
-        const int64_t most = std::max<int64_t>(1, fit), rounds = (nframes + most - 1) / most;
+        const int64_t most = rs_rd_round(q), rounds = (nframes + most - 1) / most;
         y.group = (nframes + rounds - 1) / rounds;
-        mid_bytes = (size_t)(y.group * spectra);
+        mid_bytes = (size_t)(y.group * C * cells) * 8;
         if (rs_rd_doppler_in_registers(y.group, q)) {
             // KB range bins x L / 16 threads per channel, CP channels side by
             // side; enough runs of channels for kDopplerPerCu workgroups per
@@ -151,4 +159,38 @@ inline rs_rd_layout rs_rd_plan_layout(const rs_rd_shape &q, int64_t nframes, boo
     y.parts = y.pw + rs_rd_up(pw_bytes);
     y.total = y.parts + rs_rd_up(part_bytes);
     return y;
+}
+
+// Workspace that serves any call of up to `nframes` frames: a program sizes it
+// for its largest call.  A call's own need falls here and there as frames are
+// added (fewer runs of channels; the fused path takes over with a partial map
+// per workgroup instead of the spectra).
+inline size_t rs_rd_workspace_bytes(const rs_rd_shape &q, int64_t nframes, bool power_given)
+{
+    const int64_t cells = (int64_t)q.Ns * q.L;
+    // the paths and the runs change below this many frames of a round only
+    const int64_t few = std::min(nframes, std::max<int64_t>(4096, 16 * (int64_t)q.ncu));
+    size_t mid = 0, parts = 0;
+    int groups = 0;
+    auto two_pass = [&](int64_t n) {
+        const rs_rd_layout y = rs_rd_plan_layout(q, n, true);
+        if (y.fused) return;
+        mid = std::max(mid, y.pw);
+        parts = std::max(parts, (size_t)n * y.groups);
+        groups = std::max(groups, y.groups);
+    };
+    for (int64_t n = 1; n <= few; ++n) two_pass(n);
+    const bool fused = rs_rd_fused_pays(nframes, q.C, q.Ns, q.L);
+    if (nframes > few && !fused) {
+        two_pass(std::min(nframes, rs_rd_round(q)));   // a longer call's rounds hold no more
+        parts = (size_t)nframes * groups;
+    }
+    if (fused) {
+        const int64_t items = nframes * q.C, per = (items + q.ncu - 1) / q.ncu;
+        const int64_t maps = std::min<int64_t>(q.ncu, items) * ((per + q.C - 2) / q.C + 1);
+        mid = std::max(mid, rs_rd_up((size_t)(maps * cells) * sizeof(float)));
+        parts = std::max(parts, (size_t)(nframes * (cells / kMergeCells)));
+    }
+    return mid + (power_given ? 0 : rs_rd_up((size_t)(nframes * cells) * sizeof(float))) +
+           rs_rd_up(parts * kRdPeakPartBytes);
 }

@@ -57,8 +57,35 @@ static void runs(const rs_rd_shape &q)
     }
 }
 
+// A workspace for `F` frames serves every smaller call, and is not much larger
+// than the largest of their needs.
+static void bound(const rs_rd_shape &q)
+{
+    for (int pg = 0; pg < 2; ++pg) {
+        size_t most = 0;
+        const int64_t dense = q.C <= 12 || q.C == 192 ? 900 : 120;
+        for (int64_t F = 1; F <= dense; ++F) {
+            most = std::max(most, rs_rd_plan_layout(q, F, pg).total);
+            if (F > 40 && F % 37 > 1) continue;
+            const size_t b = rs_rd_workspace_bytes(q, F, pg);
+            CHECK(b >= most && b <= 2 * most);
+        }
+        for (int64_t F : {4095, 4096, 4097, 5000, 100000, 3000001}) {
+            const size_t b = rs_rd_workspace_bytes(q, F, pg);
+            for (int64_t n = F; n > 0; n -= 1 + (F - n) * (F - n)) CHECK(rs_rd_plan_layout(q, n, pg).total <= b);
+            for (int64_t n = 1; n < F; n = n * 5 / 4 + 1) CHECK(rs_rd_plan_layout(q, n, pg).total <= b);
+            const int64_t r = rs_rd_round(q);
+            for (int64_t n : {r - 1, r, r + 1, 2 * r, 2 * r + 1, 3 * r})
+                if (n >= 1 && n <= F) CHECK(rs_rd_plan_layout(q, n, pg).total <= b);
+        }
+    }
+}
+
 int main()
 {
+    for_shapes([](const rs_rd_shape &q) {
+        if (q.Ns == 256 || q.L == 16 || q.L == 64 || q.Ns * q.L <= 16) bound(q);
+    });
     for_shapes(runs);
     std::puts("ALL OK");
     return 0;
