@@ -667,12 +667,18 @@ __device__ __forceinline__ void block_peak(float best, int bidx, rd_peak_part *p
     }
 }
 
+// Four neighbouring cells of a map: a caller's array of floats, aligned as such
+// (16-byte accesses of 4-byte alignment are one instruction here).
+struct __attribute__((packed, aligned(4))) cells4 {
+    float x, y, z, w;
+};
+
 // Stores four neighbouring cells of a map and takes them into the running
 // maximum (d = 0 skipped when skip_static).
 __device__ __forceinline__ void store_cells(float *map, int e, const float4 &s, int L, int skip_static, float &best,
                                             int &bidx)
 {
-    *reinterpret_cast<float4 *>(map + e) = s;
+    *reinterpret_cast<cells4 *>(map + e) = cells4{s.x, s.y, s.z, s.w};
     const float vals[4] = {s.x, s.y, s.z, s.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -737,7 +743,7 @@ __global__ __launch_bounds__(256) void k_map_merge(const float *slots, float *po
     const float *src = slots + f * S * (int64_t)cells + e;
 #pragma unroll 8
     for (int k = s0; k < s1; ++k) {
-        const float4 p = *reinterpret_cast<const float4 *>(src + (int64_t)k * cells);
+        const cells4 p = *reinterpret_cast<const cells4 *>(src + (int64_t)k * cells);
         s.x += p.x;
         s.y += p.y;
         s.z += p.z;

@@ -53,3 +53,25 @@ def test_rounds_of_frames(N, Ns, L, F):
     h = (F + 1) // 2
     check_rd_frames(radar, plan, cubes, [0, 1, h - 1, h, h + 1, F - 1], skip_static=True)
     plan.close()
+
+
+@pytest.mark.parametrize("N,Ns,L,F", [(5, 512, 64, 1), (3, 64, 16, 600), (4, 256, 64, 24), (1, 64, 64, 3)])
+def test_map_at_any_float(N, Ns, L, F):
+    """A power map that starts at any float of a larger array (runs of channels,
+    one run, the fused kernel, the LDS passes): the bits of an aligned one and
+    nothing beside it."""
+    import torch
+    from paper_2307_09226_amd import rs
+    radar = scenes.radar_for(1, N, Ns, L, Fs=10e6, Tb=40e-6)
+    plan = rs.rs_cube_plan(radar, rs.RS_FORM_MFMA_SPLIT16, rs.RS_C64, max_pixels=16)
+    g = torch.Generator(device="cuda:0").manual_seed(F)
+    cubes = torch.view_as_complex(torch.randn((F, N, L, Ns, 2), generator=g, device="cuda:0"))
+    want, dtime, _ = rs.range_doppler(plan, cubes)
+    n = F * Ns * L
+    for shift in (1, 2, 3):
+        big = torch.full((n + 8,), -3.0, device="cuda:0")
+        d2 = torch.empty_like(dtime)
+        rs.rs_range_doppler(plan, cubes, True, big[shift:shift + n], d2)
+        assert torch.equal(big[shift:shift + n], want.view(-1)) and torch.equal(d2, dtime)
+        assert torch.all(big[:shift] == -3.0) and torch.all(big[shift + n:] == -3.0)
+    plan.close()
