@@ -243,7 +243,9 @@ rs_status rs_plan_tune_cached(rs_plan *plan, const rs_pixels *pixels, void *cube
 rs_status rs_plan_describe(const rs_plan *plan, int64_t P, char *buf, size_t len);
 
 /* Enqueue the synthesis of one cube on `hip_stream`.  Split-K workspace is
- * kept with the plan for the stream (256 MiB at most), or taken from the
+ * kept with the plan for the stream (at most 256 MiB a plan and 1 GiB on a
+ * device over all plans; idle ones make room for others and go back to the
+ * device when an allocation of this library fails there), or taken from the
  * device's stream-ordered pool and returned in stream order.
  * Errors: RS_E_INVALID (NULL plan/pixels/cube, P < 0 or > max_pixels, NULL
  * pixel pointer with P > 0), RS_E_NOMEM, RS_E_DEVICE. */
@@ -481,8 +483,8 @@ typedef struct {
  * Deterministic.
  * Needs Ns and L powers of two, Ns <= 4096, L <= 1024 (else
  * RS_E_UNSUPPORTED).  Temporary device memory
- * (rs_range_doppler_workspace_bytes) is allocated and freed in stream
- * order.
+ * (at most rs_range_doppler_workspace_bytes) is kept with the plan or taken
+ * from the device's pool, as for rs_beat_synthesize.
  * Errors: RS_E_INVALID (NULL plan or cubes with nframes > 0, nframes < 0),
  * RS_E_UNSUPPORTED, RS_E_NOMEM, RS_E_DEVICE.  nframes = 0 does nothing. */
 rs_status rs_range_doppler(rs_plan *plan, const void *cubes, int32_t nframes, int32_t skip_static,

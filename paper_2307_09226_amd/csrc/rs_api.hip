@@ -1,6 +1,7 @@
 // Host side of the C ABI (include/rs.h): plans, single-frame and batched
 // synthesis.  All device work is enqueued on the caller's stream.
 #include "rs_api_internal.h"
+#include "rs_blocks.h"
 #include "rs_chunks.h"
 
 #include <cerrno>
@@ -159,140 +160,83 @@ rs_status rs_check_pixels(const rs_plan *pl, const rs_pixels *px)
 
 // ------------------------------------------------------------ workspaces --
 
-// The allocating calls keep their workspaces with the plan: a block per
-// stream that uses it, found again by the next call on that stream.  Taking
-// one from the device's pool and handing it back cost a NUFFT request of
-// 5,204 pixels 20 us of host time a call (45 -> 25 us; a pool of its own for
-// each plan is worse: 76 us when three plans take turns), and a call that is
-// waited for 60-90 us more, as the device's pool
-// unmaps at every synchronisation (4,057-pixel request, waited for: 99 -> 37
-// us; the 65,536-pixel NUFFT frame 197 -> 119 us).
-// At most kBlocks blocks and kKeepBytes in all; they go with the plan, and a
-// larger call on the stream replaces its block.  Sizes are rounded up by an
-// eighth at most: the runtime maps 2 MiB and more on its own (a first call
-// that needs 1.8 MB: 155 us with a block of 2 MiB, 72 us with 1.9).  A call owns its block from take to give, so calls
-// of several threads have a block each; the event recorded at give is waited
-// for at the next take, which costs nothing on the same stream and keeps a
-// stream that got the handle of a destroyed one behind its work.  Streams do
-// not take each other's blocks: that would order them.  Whatever finds no
-// block, and every call under capture, uses the device's pool.
-constexpr int kBlocks = 8;
-constexpr size_t kKeepBytes = (size_t)256 << 20;
-constexpr size_t kMinBlock = (size_t)16 << 10;
+// The device calls of the plans' kept blocks (rs_blocks.h).
+namespace {
 
-struct rs_blocks {
-    struct block {
-        void *p = nullptr;
-        size_t bytes = 0;
-        hipStream_t st = nullptr;   // the stream of its last call
-        hipEvent_t used = nullptr;  // behind that call
-        bool taken = false;
-    };
-    std::mutex m;
-    block b[kBlocks];
-    int n = 0;
-    size_t total = 0;
+struct hip_dev {
+    typedef hipStream_t stream;
+    typedef hipEvent_t event;
+    static bool ok(hipError_t e)
+    {
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess;
+    }
+    static bool create(hipEvent_t *e) { return ok(hipEventCreateWithFlags(e, hipEventDisableTiming)); }
+    static void destroy(hipEvent_t e) { (void)ok(hipEventDestroy(e)); }
+    static bool done(hipEvent_t e)
+    {
+        // no stream that a call of ours uses is being captured, but another
+        // thread's may be, and its mode may forbid queries elsewhere
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)ok(hipThreadExchangeStreamCaptureMode(&mode));
+        const bool d = ok(hipEventQuery(e));
+        (void)ok(hipThreadExchangeStreamCaptureMode(&mode));
+        return d;
+    }
+    static bool wait(hipStream_t st, hipEvent_t e) { return ok(hipStreamWaitEvent(st, e, 0)); }
+    static bool record(hipEvent_t e, hipStream_t st) { return ok(hipEventRecord(e, st)); }
+    static bool alloc(void **p, size_t bytes, hipStream_t st) { return ok(hipMallocAsync(p, bytes, st)); }
+    static bool free(void *p, hipStream_t st) { return ok(hipFreeAsync(p, st)) || ok(hipFree(p)); }
+    static void finish(hipStream_t st) { (void)ok(hipStreamSynchronize(st)); }
 };
 
-static rs_blocks::block *block_take(rs_blocks *k, size_t bytes, hipStream_t st)
-{
-    if (bytes > kKeepBytes) return nullptr;
-    size_t step = kMinBlock;   // an eighth of the power of two below
-    while (16 * step <= bytes) step <<= 1;
-    const size_t size = (bytes + step - 1) / step * step;
-    std::lock_guard<std::mutex> g(k->m);
-    rs_blocks::block *x = nullptr;   // the stream's largest block
-    for (int i = 0; i < k->n; ++i) {
-        rs_blocks::block &c = k->b[i];
-        if (!c.taken && c.p && c.st == st && (!x || c.bytes > x->bytes)) x = &c;
-    }
-    if (x) {
-        if (hipStreamWaitEvent(st, x->used, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        if (x->bytes >= bytes) {
-            x->taken = true;
-            return x;
-        }
-        if (k->total - x->bytes + size > kKeepBytes || hipFreeAsync(x->p, st) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        k->total -= x->bytes;
-        x->p = nullptr;
-    } else {
-        for (int i = 0; i < k->n; ++i)   // a place left empty by a failed allocation
-            if (!k->b[i].taken && !k->b[i].p) x = &k->b[i];
-        if (k->total + size > kKeepBytes || (!x && k->n == kBlocks)) return nullptr;
-        if (!x) x = &k->b[k->n++];
-    }
-    if (!x->used && hipEventCreateWithFlags(&x->used, hipEventDisableTiming) != hipSuccess) {
-        (void)hipGetLastError();
-        x->used = nullptr;
-        return nullptr;
-    }
-    if (hipMallocAsync(&x->p, size, st) != hipSuccess) {
-        (void)hipGetLastError();
-        x->p = nullptr;
-        return nullptr;
-    }
-    x->bytes = size;
-    x->st = st;
-    x->taken = true;
-    k->total += size;
-    return x;
-}
+}  // namespace
 
-// None of the plan's calls is in flight: the blocks go back to the device's
-// pool, which releases them at the next synchronisation.
-static void blocks_destroy(rs_blocks *k)
+struct rs_blocks : rs_block_pool<hip_dev> {
+    using rs_block_pool<hip_dev>::rs_block_pool;
+};
+
+// For an allocation that failed: gives the idle blocks of every plan on the
+// device back to it; false if there were none.
+bool rs_release_idle_blocks(int device, hipStream_t st)
 {
-    for (int i = 0; i < kBlocks; ++i) {
-        if (k->b[i].p && hipFreeAsync(k->b[i].p, nullptr) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(k->b[i].p);
-        }
-        if (k->b[i].used) (void)hipEventDestroy(k->b[i].used);
-    }
-    delete k;
+    if (!rs_blocks::release_idle(device, st)) return false;
+    hipMemPool_t pool = nullptr;
+    if (hip_dev::ok(hipDeviceGetMemPool(&pool, device))) (void)hip_dev::ok(hipMemPoolTrimTo(pool, 0));
+    return true;
 }
 
 rs_workspace::rs_workspace(const rs_plan *pl, size_t bytes, hipStream_t s) : st(s)
 {
     if (!bytes) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (pl->blocks && hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-        rs_blocks::block *x = block_take(pl->blocks, bytes, st);
+    const bool eager = hip_dev::ok(hipStreamIsCapturing(st, &cap)) && cap == hipStreamCaptureStatusNone;
+    if (pl->blocks && eager) {
+        rs_blocks::block *x = pl->blocks->take(bytes, st);
         if (x) {
             owner = pl->blocks;
-            index = (int)(x - owner->b);
+            block = x;
             p = static_cast<char *>(x->p);
             return;
         }
     }
     void *v = nullptr;
-    if (hipMallocAsync(&v, bytes, st) == hipSuccess) p = static_cast<char *>(v);
+    if (hip_dev::alloc(&v, bytes, st) ||
+        (eager && rs_release_idle_blocks(pl->device, st) && hip_dev::alloc(&v, bytes, st)))
+        p = static_cast<char *>(v);
 }
 
 rs_status rs_workspace::give(rs_status s)
 {
     if (!p) return s;
-    hipError_t e;
-    const char *what;
+    const char *what = nullptr;
     if (owner) {
-        rs_blocks::block &x = owner->b[index];
-        what = "hipEventRecord";
-        e = hipEventRecord(x.used, st);
-        if (e != hipSuccess) (void)hipStreamSynchronize(st);
-        std::lock_guard<std::mutex> g(owner->m);
-        x.taken = false;
-    } else {
+        if (!owner->give(static_cast<rs_blocks::block *>(block), st)) what = "hipEventRecord";
+    } else if (!hip_dev::ok(hipFreeAsync(p, st))) {
         what = "hipFreeAsync";
-        e = hipFreeAsync(p, st);
     }
     p = nullptr;
-    if (e != hipSuccess && s == RS_OK) s = rs_fail(RS_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
+    if (what && s == RS_OK) s = rs_fail(RS_E_DEVICE, "%s of a call's workspace failed", what);
     return s;
 }
 
@@ -530,7 +474,7 @@ static rs_status plan_common(const rs_radar *r, rs_form form, rs_dtype dtype, in
             return rs_fail(RS_E_DEVICE, "copy of the NUFFT deconvolution table failed");
         }
     }
-    pl->blocks = new (std::nothrow) rs_blocks;
+    pl->blocks = new (std::nothrow) rs_blocks(pl->device);
     *out = pl;
     return RS_OK;
 }
@@ -608,7 +552,7 @@ extern "C" void rs_plan_destroy(rs_plan *pl)
         device_guard g(pl->device);
         if (pl->d_ant) (void)hipFree(pl->d_ant);  // waits for the device: no workspace is in use after it
         if (pl->d_deconv) (void)hipFree(pl->d_deconv);
-        if (pl->blocks) blocks_destroy(pl->blocks);
+        delete pl->blocks;
     }
     delete pl;
 }

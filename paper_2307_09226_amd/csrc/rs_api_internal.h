@@ -63,8 +63,11 @@ struct rs_workspace {
 private:
     hipStream_t st;
     rs_blocks *owner = nullptr;  // the plan's blocks, or NULL for the device's pool
-    int index = 0;
+    void *block = nullptr;       // the block of them
 };
+// For an allocation that failed: gives the idle workspaces that plans keep on the
+// device back to it, in the order of st, and waits for st; false if there were none.
+bool rs_release_idle_blocks(int device, hipStream_t st);
 rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *chunk);
 size_t rs_partial_bytes(const rs_plan *pl, int32_t S);
 size_t rs_workspace_bytes(const rs_plan *pl, int32_t S);   // partials (+ chunk scales with strengths per block)

@@ -389,7 +389,13 @@ extern "C" rs_status rs_session_create(const rs_session_opts *o, rs_session **ou
             if (status == RS_OK && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess)
                 status = rs_fail(RS_E_DEVICE, "stream creation failed");
         if (status != RS_OK) break;
-        if (so.budget && hipMalloc(&s->arena, so.budget) != hipSuccess) {
+        auto arena = [&] {
+            if (hipMalloc(&s->arena, so.budget) == hipSuccess) return true;
+            (void)hipGetLastError();
+            s->arena = nullptr;
+            return false;
+        };
+        if (so.budget && !arena() && !(rs_release_idle_blocks(s->device, s->stream) && arena())) {
             status = rs_fail(RS_E_NOMEM, "arena allocation of %zu bytes failed", so.budget);
             break;
         }

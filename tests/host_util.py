@@ -7,10 +7,10 @@ import subprocess
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def run_host_test(name, tmp_path):
+def run_host_test(name, tmp_path, sanitizers="address,undefined"):
     exe = str(tmp_path / name)
     build = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer",
-                            "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-Wall", "-Wextra", "-Werror",
+                            "-fsanitize=" + sanitizers, "-fno-sanitize-recover=all", "-Wall", "-Wextra", "-Werror",
                             "-I", os.path.join(ROOT, "paper_2307_09226_amd", "csrc"),
                             os.path.join(ROOT, "tests", "csrc", name + ".cpp"), "-o", exe, "-lpthread"],
                            capture_output=True, text=True)
