@@ -198,12 +198,20 @@ struct rs_blocks : rs_block_pool<hip_dev> {
 
 // For an allocation that failed: gives the idle blocks of every plan on the
 // device back to it; false if there were none.
-bool rs_release_idle_blocks(int device, hipStream_t st)
+static bool release_idle_blocks(int device, hipStream_t st)
 {
     if (!rs_blocks::release_idle(device, st)) return false;
     hipMemPool_t pool = nullptr;
     if (hip_dev::ok(hipDeviceGetMemPool(&pool, device))) (void)hip_dev::ok(hipMemPoolTrimTo(pool, 0));
     return true;
+}
+
+void *rs_device_malloc(int device, size_t bytes, hipStream_t st)
+{
+    void *p = nullptr;
+    if (hip_dev::ok(hipMalloc(&p, bytes)) || (release_idle_blocks(device, st) && hip_dev::ok(hipMalloc(&p, bytes))))
+        return p;
+    return nullptr;
 }
 
 rs_workspace::rs_workspace(const rs_plan *pl, size_t bytes, hipStream_t s) : st(s)
@@ -222,7 +230,7 @@ rs_workspace::rs_workspace(const rs_plan *pl, size_t bytes, hipStream_t s) : st(
     }
     void *v = nullptr;
     if (hip_dev::alloc(&v, bytes, st) ||
-        (eager && rs_release_idle_blocks(pl->device, st) && hip_dev::alloc(&v, bytes, st)))
+        (eager && release_idle_blocks(pl->device, st) && hip_dev::alloc(&v, bytes, st)))
         p = static_cast<char *>(v);
 }
 
@@ -452,7 +460,8 @@ static rs_status plan_common(const rs_radar *r, rs_form form, rs_dtype dtype, in
     std::vector<double> ant(3 * (r->M + r->N));
     std::memcpy(ant.data(), r->tx_xyz, sizeof(double) * 3 * r->M);
     std::memcpy(ant.data() + 3 * r->M, r->rx_xyz, sizeof(double) * 3 * r->N);
-    if (hipMalloc(&pl->d_ant, ant.size() * sizeof(double)) != hipSuccess) {
+    pl->d_ant = static_cast<double *>(rs_device_malloc(pl->device, ant.size() * sizeof(double), nullptr));
+    if (!pl->d_ant) {
         delete pl;
         return rs_fail(RS_E_NOMEM, "hipMalloc of the antenna table failed");
     }
@@ -464,8 +473,8 @@ static rs_status plan_common(const rs_radar *r, rs_form form, rs_dtype dtype, in
     }
     if (!deconv.empty()) {
         const size_t nb = deconv.size() * sizeof(float);
-        if (hipMalloc(&pl->d_deconv, nb) != hipSuccess) {
-            pl->d_deconv = nullptr;
+        pl->d_deconv = static_cast<float *>(rs_device_malloc(pl->device, nb, nullptr));
+        if (!pl->d_deconv) {
             rs_plan_destroy(pl);
             return rs_fail(RS_E_NOMEM, "hipMalloc of the NUFFT deconvolution table failed");
         }

@@ -65,9 +65,10 @@ private:
     rs_blocks *owner = nullptr;  // the plan's blocks, or NULL for the device's pool
     void *block = nullptr;       // the block of them
 };
-// For an allocation that failed: gives the idle workspaces that plans keep on the
-// device back to it, in the order of st, and waits for st; false if there were none.
-bool rs_release_idle_blocks(int device, hipStream_t st);
+// hipMalloc on the current device, which is `device`; where memory is short, once
+// more after the idle workspaces that plans keep there went back to it, in the
+// order of st.  NULL if that fails too; no error is left behind.
+void *rs_device_malloc(int device, size_t bytes, hipStream_t st);
 rs_status rs_plan_chunking(const rs_plan *pl, int64_t P, int32_t *S, int32_t *chunk);
 size_t rs_partial_bytes(const rs_plan *pl, int32_t S);
 size_t rs_workspace_bytes(const rs_plan *pl, int32_t S);   // partials (+ chunk scales with strengths per block)

@@ -389,20 +389,15 @@ extern "C" rs_status rs_session_create(const rs_session_opts *o, rs_session **ou
             if (status == RS_OK && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess)
                 status = rs_fail(RS_E_DEVICE, "stream creation failed");
         if (status != RS_OK) break;
-        auto arena = [&] {
-            if (hipMalloc(&s->arena, so.budget) == hipSuccess) return true;
-            (void)hipGetLastError();
-            s->arena = nullptr;
-            return false;
-        };
-        if (so.budget && !arena() && !(rs_release_idle_blocks(s->device, s->stream) && arena())) {
+        auto device_malloc = [&](size_t bytes) { return rs_device_malloc(s->device, bytes, s->stream); };
+        if (so.budget && !(s->arena = static_cast<char *>(device_malloc(so.budget)))) {
             status = rs_fail(RS_E_NOMEM, "arena allocation of %zu bytes failed", so.budget);
             break;
         }
         // a matrix-core plan has at most one chunk per compute unit
         s->scale_row = (size_t)s->ncu;
-        if (hipMalloc(reinterpret_cast<void **>(&s->scales), sizeof(int32_t) * s->scale_row * so.max_slots) !=
-            hipSuccess) {
+        s->scales = static_cast<int32_t *>(device_malloc(sizeof(int32_t) * s->scale_row * so.max_slots));
+        if (!s->scales) {
             status = rs_fail(RS_E_NOMEM, "scale pool allocation failed");
             break;
         }
@@ -410,8 +405,8 @@ extern "C" rs_status rs_session_create(const rs_session_opts *o, rs_session **ou
         for (auto &rg : s->ring) {
             if (hipHostMalloc(reinterpret_cast<void **>(&rg.h_jobs), sizeof(rs_job) * s->jobs_cap,
                               hipHostMallocDefault) != hipSuccess ||
-                hipMalloc(&rg.d_jobs, sizeof(rs_job) * s->jobs_cap) != hipSuccess ||
-                hipMalloc(&rg.d_counter, sizeof(int) * 64) != hipSuccess ||
+                !(rg.d_jobs = static_cast<rs_job *>(device_malloc(sizeof(rs_job) * s->jobs_cap))) ||
+                !(rg.d_counter = static_cast<int *>(device_malloc(sizeof(int) * 64))) ||
                 hipEventCreateWithFlags(&rg.done, hipEventDisableTiming) != hipSuccess ||
                 hipEventCreateWithFlags(&rg.start, hipEventDisableTiming) != hipSuccess) {
                 status = rs_fail(RS_E_NOMEM, "session ring allocation failed");
