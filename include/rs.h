@@ -225,7 +225,9 @@ rs_status rs_plan_tune(rs_plan *plan, const rs_pixels *pixels, void *cube, int32
 /* rs_plan_tune with a persistent cache of its choices: a text file at
  * cache_path (host path), one entry per line "C Ns L Pb TILE" keyed by the
  * channel count, N_s, L and Pb, the pixel count rounded up to a power of
- * two, TILE a configuration string as above.  On a hit (the last
+ * two, TILE a configuration string as above; complex128 plans, which run
+ * another kernel, read and write "C Ns L Pb TILE complex128" and skip the
+ * shorter lines, complex64 plans the other way round.  On a hit (the last
  * well-formed line with the plan's key and a built configuration) the plan
  * takes that configuration and nothing is launched; on a miss the
  * configuration is tuned as rs_plan_tune does (the cube is synthesised) and

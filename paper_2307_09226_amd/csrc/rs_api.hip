@@ -744,6 +744,9 @@ extern "C" rs_status rs_plan_tune_cached(rs_plan *pl, const rs_pixels *px, void 
     }
     long long pb = 1;
     while (pb < px->P) pb <<= 1;
+    // complex128 plans run another kernel, with other tile costs: their entries
+    // say so in a sixth field (entries without it are complex64 plans')
+    const char *const kind = pl->mirror ? "" : "complex128";
     // the last well-formed entry with this key and a built shape wins
     int hit_wn = 0, hit_tl = 0, hit_nw = 0, hit_il = 0;
     if (std::FILE *f = std::fopen(cache_path, "r")) {
@@ -751,9 +754,10 @@ extern "C" rs_status rs_plan_tune_cached(rs_plan *pl, const rs_pixels *px, void 
         while (std::fgets(line, sizeof line, f)) {
             int c = 0, ns = 0, l = 0, wn = 0, tl = 0, nw = 0, il = 0;
             long long b = 0;
-            char tile[64];
-            if (std::sscanf(line, "%d %d %d %lld %63s", &c, &ns, &l, &b, tile) == 5 && c == pl->C &&
-                ns == pl->Ns && l == pl->L && b == pb && parse_tile(tile, &wn, &tl, &nw, &il)) {
+            char tile[64], what[32];
+            const int n = std::sscanf(line, "%d %d %d %lld %63s %31s", &c, &ns, &l, &b, tile, what);
+            if (n >= 5 && std::strcmp(n == 6 && !std::strcmp(what, "complex128") ? what : "", kind) == 0 &&
+                c == pl->C && ns == pl->Ns && l == pl->L && b == pb && parse_tile(tile, &wn, &tl, &nw, &il)) {
                 hit_wn = wn;
                 hit_tl = tl;
                 hit_nw = nw;
@@ -774,7 +778,7 @@ extern "C" rs_status rs_plan_tune_cached(rs_plan *pl, const rs_pixels *px, void 
     if ((s = rs_plan_tune(pl, px, cube, reps, stream, chosen, chosen_len)) != RS_OK) return s;
     char tile[32], entry[128];
     format_tile(pl, tile, sizeof tile);
-    snprintf(entry, sizeof entry, "%d %d %d %lld %s\n", pl->C, pl->Ns, pl->L, pb, tile);
+    snprintf(entry, sizeof entry, "%d %d %d %lld %s%s%s\n", pl->C, pl->Ns, pl->L, pb, tile, *kind ? " " : "", kind);
     std::FILE *f = std::fopen(cache_path, "a");
     const bool ok = f && std::fputs(entry, f) >= 0;
     if (f && std::fclose(f) != 0) return rs_fail(RS_E_INVALID, "cannot append to the tile cache %s", cache_path);
