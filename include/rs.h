@@ -211,9 +211,11 @@ rs_status rs_plan_set_tile(rs_plan *plan, const char *tile);
 /* Chooses the matrix-core tile configuration of `plan` by measurement:
  * every built configuration (the eight shapes, and the three 8-wave shapes
  * again with 'i') synthesises `pixels` into `cube` once to warm up and
- * `reps` times timed with HIP events on `hip_stream`, and the one with the
- * smallest mean time is kept (the plan's own choice otherwise comes from a
- * rule measured on full launches).  The call synchronises
+ * `reps` times timed with HIP events on `hip_stream`, between runs of the
+ * plan's present one, which come first until their time is steady.  The
+ * fastest relative to those is taken if it is faster in five more such runs;
+ * else the plan keeps what it has (a rule measured on full launches, or the
+ * last choice).  The call synchronises
  * the stream and leaves the last synthesis in `cube`.  It changes the plan:
  * call it before the plan is shared, never while other calls use it.  Plans
  * of the other forms are left unchanged.  chosen (may be NULL) receives the

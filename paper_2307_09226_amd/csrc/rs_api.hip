@@ -3,6 +3,7 @@
 #include "rs_api_internal.h"
 #include "rs_blocks.h"
 #include "rs_chunks.h"
+#include "rs_tune.h"
 
 #include <cerrno>
 #include <cmath>
@@ -693,31 +694,27 @@ extern "C" rs_status rs_plan_tune(rs_plan *pl, const rs_pixels *px, void *cube, 
             if (e0) (void)hipEventDestroy(e0);
             return rs_fail(RS_E_DEVICE, "hipEventCreate failed");
         }
-        const int wn0 = pl->wn, tl0 = pl->tl, nw0 = pl->nw, il0 = pl->interleave;
-        int best = -1;
-        float best_ms = 0.f;
-        for (int i = 0; i < (int)(sizeof shapes / sizeof shapes[0]) && s == RS_OK; ++i) {
-            if (!rs_mfma_shape_supported(shapes[i][0], shapes[i][1], shapes[i][2])) continue;
-            set_mfma_shape(pl, shapes[i][0], shapes[i][1], shapes[i][2], shapes[i][3]);
-            if ((s = rs_beat_synthesize(pl, px, cube, stream)) != RS_OK) break;
+        constexpr int n = sizeof shapes / sizeof shapes[0];
+        auto set = [&](int i) { set_mfma_shape(pl, shapes[i][0], shapes[i][1], shapes[i][2], shapes[i][3]); };
+        int own = 0;   // every plan's shape is one of them
+        for (int i = 0; i < n; ++i)
+            if (shapes[i][0] == pl->wn && shapes[i][1] == pl->tl && shapes[i][2] == pl->nw && shapes[i][3] == pl->interleave)
+                own = i;
+        const int best = rs_tune_pick(n, own, [&](int i) -> double {
+            set(i);
+            if ((s = rs_beat_synthesize(pl, px, cube, stream)) != RS_OK) return -1.0;
             (void)hipEventRecord(e0, st);
             for (int r = 0; r < reps && s == RS_OK; ++r) s = rs_beat_synthesize(pl, px, cube, stream);
             (void)hipEventRecord(e1, st);
             float ms = 0.f;
             if (s == RS_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
                 s = rs_fail(RS_E_DEVICE, "event timing failed");
-            if (s == RS_OK && (best < 0 || ms < best_ms)) {
-                best = i;
-                best_ms = ms;
-            }
-        }
+            return s == RS_OK ? (double)ms : -1.0;
+        });
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-        if (s != RS_OK || best < 0) {
-            set_mfma_shape(pl, wn0, tl0, nw0, il0);
-            return s != RS_OK ? s : rs_fail(RS_E_UNSUPPORTED, "no tile shape could run");
-        }
-        set_mfma_shape(pl, shapes[best][0], shapes[best][1], shapes[best][2], shapes[best][3]);
+        set(best < 0 ? own : best);
+        if (best < 0) return s;
         // leave the cube computed with the chosen shape
         if ((s = rs_beat_synthesize(pl, px, cube, stream)) != RS_OK) return s;
         if (hipStreamSynchronize(st) != hipSuccess) return rs_fail(RS_E_DEVICE, "stream synchronisation failed");
