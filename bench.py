@@ -39,12 +39,12 @@ FLOP_PLAIN = 4         # 2 binary64 real MACs (a mirrored sample pair shares 4)
 # the kernel sources they were taken on; any change to those sources turns
 # the figure into null until the counters are taken again.
 TRAFFIC = {"sources": ("rs_mirror.hip", "rs_device.h", "rs_internal.h", "rs_split16.h"),
-           "sources_sha256": "6e9b24fa56a2fa023ae20047286c2e82fb44d1d0df3a7df43d2f0425f9c5ee14",
+           "sources_sha256": "efbe3fbfa71bda975290037736532ffec5ecc64c5c39343a4e60018a26b6d6b1",
            "fetch_bytes": 2.0 * 6873 * 1024, "write_bytes": 71064 * 1024}
 # The same for one rs_range_doppler_ws call on the 100-frame walk (k_rd_fused,
 # k_rd_merge, k_rd_peak summed).
-RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_fft.h"),
-              "sources_sha256": "f2c047fa871e4e8fb97129bba6c78d11f724e03ec90261f78e98236317362f6b",
+RD_TRAFFIC = {"sources": ("rs_rd.hip", "rs_rd_layout.h", "rs_fft.h"),
+              "sources_sha256": "81292070dd5506df7b989d18c3d1d702a7fe34b8c89aee1b1ad8e7494f5c4183",
               "fetch_bytes": 2.0 * (158860 + 20534 + 52) * 1024, "write_bytes": (42880 + 12825 + 55) * 1024}
 
 

@@ -34,11 +34,13 @@
  *                         per-channel complex contraction
  *                         Y_c = F_c^T diag(sigma_c) D done on fp16 matrix
  *                         cores with fp32 accumulation (hi*hi + hi*lo +
- *                         lo*hi): complex128 plans sample by sample,
- *                         complex64 plans with fast time taken from its
- *                         middle, mirrored samples sharing their cosine and
- *                         sine sums (half the products).  Typical relative L2 error vs an exact
- *                         binary64 sum: 1e-6 .. 1e-5.
+ *                         lo*hi): complex64 plans with fast time taken from
+ *                         its middle, mirrored samples sharing their cosine
+ *                         and sine sums (half the products); complex128
+ *                         plans sample by sample, as they always were, so
+ *                         that their cubes keep their bits.  Typical
+ *                         relative L2 error vs an exact binary64 sum, in
+ *                         either type: 1e-6 .. 1e-5.
  *   RS_FORM_NUFFT         per channel a two-dimensional type-1 non-uniform
  *                         FFT from the points (b, -beta) onto the Ns x L
  *                         modes: binary64 phase arguments, float32

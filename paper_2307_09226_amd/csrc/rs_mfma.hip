@@ -1,9 +1,10 @@
 // Split-FP16 matrix-core form, sample by sample (gfx950,
-// v_mfma_f32_32x32x16_f16): the kernel of complex128 plans.  complex64 plans
-// run rs_mirror.hip, which takes half the products (65,536-pixel frame: 0.25
-// ms against 0.38 ms) and rounds differently, by 1e-6 relative: within the
-// form's error and a complex64 value's use, but a complex128 cube is compared
-// and stored at 1e-9 and below, so its values stay what they were, bit for bit.
+// v_mfma_f32_32x32x16_f16): the kernel of complex128 plans, whose cubes keep the
+// order of sums, and so the bits, that they have had.  complex64 plans run
+// rs_mirror.hip, which takes half the products (65,536-pixel frame: 0.25 ms
+// against 0.38 ms), is closer to the exact sum (full cubes of 2,048 pixels: 4.4e-7
+// against 5.7e-7) and differs from this one by 1e-6 relative.  Nothing in the form
+// asks for this one: a complex128 cube has the form's error too.
 //
 // For one virtual channel c the cube is the complex contraction over pixels
 //   Y_c[n][l] = sum_p F_c[p][n] * D[p][l]

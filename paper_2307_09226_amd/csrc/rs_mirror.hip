@@ -67,7 +67,12 @@
 // of every chunk.  The raw fp32 accumulators are then parked in the partial
 // buffer (C at a pair's upper sample, S at its lower one) and reloaded by the
 // next segment, which makes the result independent of how a chunk is split
-// into segments.
+// into segments.  The middle sample of an odd Ns (k = 0) is its own mirror and has
+// room for C alone: its sine operand has to be exactly 0.  It is: where the
+// phasor comes by a rotation back from index LQ, both factors are the sine and
+// cosine s, c of the same reduced phase, the residue s c - rn(s c) is at most
+// 2^-26, and both fp16 halves of that are 0 (2^-25 rounds to 0); where it is
+// evaluated, its phase is 0.
 #include "rs_device.h"
 #include "rs_split16.h"
 
