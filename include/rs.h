@@ -481,7 +481,7 @@ typedef struct {
  *                                           its velocity spectrum at the peak
  *   peaks         rs_rd_peak [nframes]
  * Arithmetic in float32 with twiddles from binary64.  Many frames with
- * Ns = 256 and L = 64 or 128: each channel's 2-D FFT runs in registers and LDS
+ * Ns = 256 and L = 64 or 128 (of few channels also L = 32): each channel's 2-D FFT runs in registers and LDS
  * within one workgroup and the channels' power is summed in registers
  * (partial maps of the workgroups that share a frame are added in a fixed
  * order); otherwise a fast-time pass into the workspace and a slow-time pass

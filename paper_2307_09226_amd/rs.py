@@ -416,7 +416,9 @@ def rs_render_scenes(scenes_, g_az: int, g_el: int, noise=None, device="cuda:0",
     """Ray-cast len(scenes_) frames on the device.  scenes_: rs_scene records
     or a scene_array(); noise: device float32 [F * P] strength factors or
     None; out: five float32 [F * P] device tensors to fill, or None for new
-    ones.  Returns one DevicePixels per frame (views into the five tensors)."""
+    ones.  Returns one DevicePixels per frame (views into the five tensors,
+    made together: an in-place operation on one of them cannot record
+    gradients; clone it first)."""
     import torch
     F = len(scenes_)
     P = int(g_az) * int(g_el)
